@@ -193,6 +193,14 @@ ibb_status ibb_lattice_count(const ibb_desc *desc, int kind, int axis, int64_t *
  * max_springs springs. */
 ibb_status ibb_footprint_bytes(const ibb_desc *desc, int64_t max_nodes, int64_t max_springs, size_t *bytes);
 
+/* Device memory with which a context's own solves (not those of a group it
+ * belongs to) run whole V-cycles of its smaller levels in one launch: the
+ * same results, sooner.  Optional; *bytes is 0 where the context has no use
+ * for it.  The memory is the caller's, stays until the context is destroyed,
+ * and is set at most once, between calls that solve. */
+ibb_status ibb_solver_scratch_bytes(ibb_ctx *ctx, size_t *bytes);
+ibb_status ibb_set_solver_scratch(ibb_ctx *ctx, void *scratch, size_t bytes);
+
 /* --- lifetime ------------------------------------------------------------ */
 
 /* Validate desc, carve the workspace and set every field to zero.  The

@@ -116,6 +116,8 @@ ABI_FUNCTIONS = {
     "ibb_lattice_count": (ctypes.c_int, [DESC, ctypes.c_int, ctypes.c_int, ctypes.POINTER(I64),
                                          ctypes.POINTER(ctypes.c_int)]),
     "ibb_footprint_bytes": (ctypes.c_int, [DESC, I64, I64, ctypes.POINTER(ctypes.c_size_t)]),
+    "ibb_solver_scratch_bytes": (ctypes.c_int, [CTX, ctypes.POINTER(ctypes.c_size_t)]),
+    "ibb_set_solver_scratch": (ctypes.c_int, [CTX, VP, ctypes.c_size_t]),
     "ibb_create": (ctypes.c_int, [DESC, I64, I64, VP, ctypes.c_size_t, VP, ctypes.POINTER(CTX)]),
     "ibb_destroy": (ctypes.c_int, [CTX]),
     "ibb_set_state": (ctypes.c_int, [CTX, VP, VP]),

@@ -8,10 +8,12 @@
 
 #include <algorithm>
 #include <mutex>
+#include <atomic>
 #include <string>
 #include <vector>
 
 #include "../../include/ibmg.h"
+#include "bricks.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -103,6 +105,21 @@ struct ibb_ctx {
     Tail tail[2] = {};
     LdsLevel *tplan[2] = {};
     int tplan_bytes[2] = {};
+    // the levels run as bricks per system (0 pressure, 1 velocity): the
+    // levels above the one-workgroup cycle's tail that fit, from bplan.lm to
+    // bplan.lc, in the precision of the context's V-cycles (planned, and run
+    // so once the solver scratch is there); mailboxes per level and the
+    // control block, shared by the two systems (their solves follow each
+    // other on one stream)
+    bool planned[2] = {false, false}, bricks[2] = {false, false};
+    BrickPlan bplan[2] = {};
+    BrickPlan *bplan_dev[2] = {};
+    unsigned long long *bmx[MAXLEV] = {}, *bmb[MAXLEV] = {};
+    BrickCtl *bctl = nullptr;     // behind the scalar, read back with it
+    // launch pass by pass although there are bricks (see pass_by_pass), and
+    // for good once a launch of bricks did not find its workgroups together
+    bool plain = false, apart = false;
+    int dev = 0;
     // nodes and springs
     long long eta_max = 0, m_max = 0;
     int eta = 0, m = 0;
@@ -129,10 +146,11 @@ struct ibb_ctx {
     // (pressure, velocity), captured once on a private stream and replayed
     // on the context's stream
     hipStream_t cap = nullptr;
-    hipGraphExec_t tick[2] = {};
+    // (with bricks, and without)
+    hipGraphExec_t tick[2][2] = {};
     // GCR: one graph per system and position in the restart window (the
     // number of Gram-Schmidt steps depends on it)
-    std::vector<hipGraphExec_t> gtick[2];
+    std::vector<hipGraphExec_t> gtick[2][2];
     // finest-level kernel timing (ibb_profile_*)
     bool prof = false;
     std::vector<hipEvent_t> pev;           // pairs: start, stop
@@ -413,6 +431,7 @@ size_t carve(ibb_ctx *c, char *base, bool dry)
     }
     c->partial = cv.take<double>(3 * NORM_BLOCKS_MAX);
     c->scalar = cv.take<double>(8);
+    static_assert(sizeof(BrickCtl) + sizeof(double) <= 8 * sizeof(double), "the control block fits behind the scalar");
     const size_t em = (size_t)(c->eta_max > 0 ? c->eta_max : 1);
     const size_t mm = (size_t)(c->m_max > 0 ? c->m_max : 1);
     c->X = cv.take<double>(3 * em);
@@ -456,6 +475,40 @@ size_t carve(ibb_ctx *c, char *base, bool dry)
     return cv.off + 256;
 }
 
+// the solver scratch: mailboxes, plans and tables of the bricks
+size_t carve_bricks(ibb_ctx *c, char *base, bool dry)
+{
+    Carver cv{base, 0, dry};
+    if (!c->planned[0] && !c->planned[1]) return 0;
+    // a dry run leaves the context as it is: it may be running with them
+    auto put = [&](auto *&at, auto *got) {
+        if (!dry) at = got;
+    };
+    const int D = c->d.dim;
+    const bool refined = c->d.precision == IBB_FP32_REFINED;
+    const size_t words = (size_t)brick_mail_words(refined ? 4 : 8);
+    for (int l = 0; l < c->L; ++l) {
+        bool used = false;
+        for (int v = 0; v < 2; ++v)
+            used = used || (c->planned[v] && l >= c->bplan[v].lm && l <= c->bplan[v].lc + 1);
+        if (!used) continue;
+        put(c->bmx[l], cv.take<unsigned long long>((size_t)D * c->lv[l].g.nel * words));
+        put(c->bmb[l], cv.take<unsigned long long>((size_t)D * c->lv[l].g.nel * words));
+    }
+    for (int v = 0; v < 2; ++v) {
+        put(c->bplan_dev[v], cv.take<BrickPlan>(1));
+        if (!c->planned[v]) continue;
+        for (int l = c->bplan[v].lm; l <= c->bplan[v].lc + 1; ++l) {
+            BrickLev &b = c->bplan[v].lev[l];
+            const size_t n = (size_t)b.sy * b.sz;
+            put(b.slots, static_cast<void *>(cv.take<int4>(n * (b.os + b.rs) * BRICK_THREADS)));
+            put(b.from_x, cv.take<unsigned>(n * b.nx));
+            put(b.from_s, cv.take<unsigned>(n * b.ns));
+        }
+    }
+    return cv.off + 256;
+}
+
 // LDS per workgroup that the tail decision assumes (gfx950: 160 KB, less
 // the kernels' own shared data); fixed, so that footprints do not depend on
 // the device queried
@@ -473,6 +526,195 @@ long long tail_lds_bytes(const ibb_ctx *c, bool f32, bool vel, int lt)
     long long b = 0;
     for (int l = lt; l < c->L; ++l) b += (long long)arena_array_bytes(c->lv[l].g, f32 ? 4 : 8) * (nsolve + ncoef);
     return b;
+}
+
+// LDS of a brick workgroup: the CU's, less the kernel's own shared data;
+// fixed, as TAIL_LDS_BUDGET
+constexpr int BRICK_LDS_BUDGET = 163840 - (int)(TAIL_MAX * sizeof(double)) - 256;
+// a workgroup that has waited this long for the others to start (100 MHz
+// ticks: 20 ms) runs the cycle by itself
+constexpr long long BRICK_WAIT = 2000000;
+
+// How level l is cut into bricks: boxes of cy x cz lines, at most `cap` of
+// them, with the least time per colour pass, taken as the passes of
+// BRICK_THREADS points and of half as many polls for the surface; boxes keep
+// at least 64 points a colour (a wave) where the level has them.  `small`:
+// the tail's level, whose boxes only share out the restriction and the rows.
+bool brick_boxes(const Grid &g, int cap, bool small, BrickLev &b)
+{
+    const int D = g.D, n1 = g.n[1], n2 = D == 3 ? g.n[2] : 1;
+    const int hx = ((g.bc[0] == AX_INOUT ? g.n[0] : g.n[0] - 1) + 2) >> 1;
+    const int e1 = g.bc[1] == AX_INOUT ? 1 : 0, e2 = D == 3 && g.bc[2] == AX_INOUT ? 1 : 0;
+    double best = 1e30;
+    for (int cy = 1; cy < 2 * n1; cy *= 2)
+        for (int cz = 1; cz < 2 * n2; cz *= 2) {
+            const int by = std::min(cy, n1), bz = std::min(cz, n2);
+            const int sy = (n1 + by - 1) / by, sz = (n2 + bz - 1) / bz;
+            if (sy * sz > cap) continue;
+            const int ly = by + e1, lz = bz + e2;
+            const int own = ly * lz * hx;
+            const int ring = D == 3 ? (ly + 2) * (lz + 2) - ly * lz : 2;
+            if (std::max(own, ring * hx) > BRICK_SLOTS * BRICK_THREADS) continue;
+            double cost = std::max(0.25, own / (double)BRICK_THREADS) + 0.5 * ring * hx / (double)BRICK_THREADS;
+            if (!small && by * bz * hx < 64) cost += 1.0;
+            if (cost >= best) continue;
+            best = cost;
+            b.cy = by;
+            b.cz = bz;
+            b.sy = sy;
+            b.sz = sz;
+        }
+    return best < 1e30;
+}
+
+// the passes over a level's components as uniform offsets
+void brick_passes(const Grid &g, bool vel, int wsz, BrickLev &b)
+{
+    const int D = g.D, nc = vel ? D : 1, role = vel ? ROLE_V : ROLE_P;
+    const int step[3] = {wsz, g.NX * wsz, b.wy * g.NX * wsz};
+    const int cell[3] = {wsz, g.NX * wsz, (int)g.NXY * wsz};
+    for (int a = 0; a < nc; ++a) {
+        BrickPass &P = b.pass[a];
+        P = BrickPass{};
+        int ax[3];
+        if (vel) {
+            ax[0] = a;
+            for (int n = 1, d = 0; d < 3; ++d)
+                if (d != a) ax[n++] = d;
+        } else {
+            for (int d = 0; d < 3; ++d) ax[d] = d;
+        }
+        auto arr = [&](int k, int off) { return (unsigned)k * b.stride + (unsigned)off; };
+        P.coef[0] = arr(vel ? 4 + 5 * a : 1, 0);
+        P.coef[1] = arr(6 + 5 * a, 0);
+        if (vel) {
+            P.coef[2] = arr(3 + 5 * D, 0);
+            P.coef[3] = arr(3 + 5 * D, -cell[a]);
+        }
+        for (int n = 0; n < D; ++n) {
+            const int d = ax[n];
+            P.win[n] = vel ? d * b.wn * wsz : 0;
+            P.step[n] = step[d];
+            P.axis[n] = 2 + 2 * d;
+            if (g.bc[d] == AX_WALLS) P.walls |= 1 << n;
+            if (g.bc[d] != AX_PERIODIC) P.edge |= 3 << (2 + 2 * d);
+            if (!vel) {
+                P.coef[2 + 2 * n] = arr(7 + 5 * d, cell[d]);
+                P.coef[3 + 2 * n] = arr(7 + 5 * d, 0);
+            } else if (n > 0) {
+                const int me = 4 + 5 * D + (D == 3 ? 3 - a - d : 0);
+                P.coef[2 + 2 * n] = arr(me, cell[d]);
+                P.coef[3 + 2 * n] = arr(me, 0);
+            }
+        }
+        for (int d = 0; d < D; ++d) {
+            const int vert = vel && d == a;
+            for (int q = 0; q <= g.n[d]; ++q) {
+                const AxisImages m = images_of(g, d, vert, role, q);
+                for (int e = 0; e < 2; ++e)
+                    if (m.s[e]) {
+                        P.img[d][e] = (m.q[e] - q) * step[d];
+                        if (m.s[e] < 0) P.odd |= 1 << (2 * d + e);
+                    }
+            }
+        }
+        unk_range(g, 0, vel && a == 0, P.xlo, P.xhi);
+        P.mail = (unsigned)(a * g.nel * brick_mail_words(wsz));
+        P.face_x = vel && a == 0 ? 1 : 0;
+    }
+}
+
+// The levels of system vel that run as bricks: from the level above the tail
+// upwards while the boxes fit the workgroups of the chip and their windows
+// the LDS.  Measured on levels of 64 x 64 x 128 and smaller: a launched pass
+// takes 4.0-6.3 us, a brick's 1.5-3 us; steps of 64 x 64 x 128 in FP32 went
+// from 34.9 to 27.1 ms, 48 x 48 x 96 from 43.7 to 36.3, in FP64 64 x 64 x 128
+// from 38.9 to 35.8 and 32 x 32 x 32 from 43.0 to 41.0, 128 x 64 from 24.8 to
+// 20.8 and 64 x 32 from 15.3 to 14.9.
+bool plan_bricks(const ibb_ctx *c, bool vel, BrickPlan &P)
+{
+    const ibb_desc *d = &c->d;
+    const int D = d->dim, nc = vel ? D : 1;
+    const int wsz = d->precision == IBB_FP32_REFINED ? 4 : 8;
+    const Tail &t = c->tail[vel ? 1 : 0];
+    P = BrickPlan{};
+    if (t.n <= 0 || t.level < 1 || d->nu1 < 1 || d->nu2 < 1) return false;
+    // the other smoothers have no bricks
+    if ((d->smoother_passes != 0 && d->smoother_passes != 2) || d->smoother_zblock > 0) return false;
+    P.lc = t.level - 1;
+    if (!brick_boxes(c->lv[t.level].g, 16, true, P.lev[t.level])) return false;
+    int lm = -1;
+    for (int l = P.lc; l >= 0; --l) {
+        const Grid &g = c->lv[l].g;
+        if (g.n[0] < 4 || g.n[0] > 1000 || g.n[1] < 4 || (D == 3 && g.n[2] < 4)) break;
+        BrickLev &b = P.lev[l];
+        if (!brick_boxes(g, BRICK_MAX_WG, false, b)) break;
+        // the windows of the levels lie one after the other; a transfer
+        // between q - 1 and q uses the place from the windows of q on: the
+        // residual of the own lines, the x sums around the coarse box (both
+        // for all components at once where that fits, else one by one), or
+        // the coarse iterate around the fine box
+        int off = 0, need = 0;
+        for (int q = l; q <= t.level; ++q) {
+            const Grid &h = c->lv[q].g;
+            BrickLev &x = P.lev[q];
+            const int e1 = h.bc[1] == AX_INOUT ? 1 : 0, e2 = h.bc[2] == AX_INOUT ? 1 : 0;
+            x.lds = off;
+            x.wy = x.cy + e1 + 2;
+            x.wn = h.NX * x.wy * (D == 3 ? x.cz + e2 + 2 : 1);
+            if (q > l) {
+                const Grid &f = c->lv[q - 1].g;
+                BrickLev &y = P.lev[q - 1];
+                const int own = f.NX * (y.cy + e1) * (D == 3 ? y.cz + e2 : 1) * wsz;
+                const int sums = (h.n[0] + 1) * (2 * (x.cy + e1) + 2) * (D == 3 ? 2 * (x.cz + e2) + 2 : 1) * 8;
+                const int one = std::max(own, sums);
+                y.gs = off + nc * one <= BRICK_LDS_BUDGET ? nc : 1;
+                const int plines = nc * ((y.cy + 1) / 2 + 4) * (D == 3 ? (y.cz + 1) / 2 + 4 : 1);
+                const int slines = nc * (2 * (x.cy + e1) + 2) * (D == 3 ? 2 * (x.cz + e2) + 2 : 1);
+                const int prl = plines * h.NX * wsz;
+                y.nx = plines * h.NX;
+                x.ns = slines * (h.n[0] + 1);
+                need = std::max(need, off + std::max(y.gs * one, prl));
+            }
+            if (q < t.level) off += ((x.wn * nc * wsz + 15) / 16) * 16;
+            need = std::max(need, off);
+        }
+        if (need > BRICK_LDS_BUDGET) break;
+        lm = l;
+        P.lds_bytes = need;
+    }
+    if (lm < 0) return false;
+    P.lm = lm;
+    for (int l = 0; l < lm; ++l) P.lev[l] = BrickLev{};
+    int off = 0;
+    P.nwg = 1;
+    for (int l = lm; l <= t.level; ++l) {
+        BrickLev &x = P.lev[l];
+        x.lds = off;
+        if (l < t.level) {
+            // as laid out above from lm
+            const Grid &f = c->lv[l].g, &h = c->lv[l + 1].g;
+            const BrickLev &y = P.lev[l + 1];
+            const int e1 = h.bc[1] == AX_INOUT ? 1 : 0, e2 = h.bc[2] == AX_INOUT ? 1 : 0;
+            const int own = f.NX * (x.cy + e1) * (D == 3 ? x.cz + e2 : 1) * wsz;
+            const int sums = (h.n[0] + 1) * (2 * (y.cy + e1) + 2) * (D == 3 ? 2 * (y.cz + e2) + 2 : 1) * 8;
+            off += ((x.wn * nc * wsz + 15) / 16) * 16;
+            x.gs = off + nc * std::max(own, sums) <= BRICK_LDS_BUDGET ? nc : 1;
+        }
+        {
+            const Grid &h = c->lv[l].g;
+            const int hx = ((h.bc[0] == AX_INOUT ? h.n[0] : h.n[0] - 1) + 2) >> 1;
+            const int ly = x.cy + (h.bc[1] == AX_INOUT ? 1 : 0), lz = D == 3 ? x.cz + (h.bc[2] == AX_INOUT ? 1 : 0) : 1;
+            const int ring = D == 3 ? (ly + 2) * (lz + 2) - ly * lz : 2;
+            x.os = (ly * lz * hx + BRICK_THREADS - 1) / BRICK_THREADS;
+            x.rs = (ring * hx + BRICK_THREADS - 1) / BRICK_THREADS;
+        }
+        x.stride = (unsigned)(((size_t)c->lv[l].g.nel * wsz + 255) & ~(size_t)255);
+        brick_passes(c->lv[l].g, vel, wsz, x);
+        P.nwg = std::max(P.nwg, x.sy * x.sz);
+    }
+    if (P.nwg > 8) P.nwg = ((P.nwg + 7) / 8) * 8;
+    return true;
 }
 
 void setup_shapes(ibb_ctx *c, const ibb_desc *d, int64_t max_nodes, int64_t max_springs)
@@ -533,6 +775,7 @@ void setup_shapes(ibb_ctx *c, const ibb_desc *d, int64_t max_nodes, int64_t max_
         c->tail[v].n = (int)n;
         c->tail[v].level = lt;
     }
+    for (int v = 0; v < 2; ++v) c->planned[v] = plan_bricks(c, v == 1, c->bplan[v]);
     // z-blocked colour passes on every 3D level when asked for (measured
     // slower than the flat passes, so not the default)
     for (int l = 0; l < c->L; ++l) c->lv[l].zb = d->dim == 3 && d->smoother_zblock > 0 ? 1 : 0;
@@ -914,9 +1157,25 @@ const LevTab<double> *level_table<double>(ibb_ctx *c) { return c->tab64; }
 template <>
 const LevTab<float> *level_table<float>(ibb_ctx *c) { return c->tab32; }
 
+// ncyc V-cycles from the first brick level down and back (xzero: its iterate
+// is zero)
+template <typename T>
+void brick_cycles(ibb_ctx *c, bool vel, int ncyc, bool xzero)
+{
+    const int v = vel ? 1 : 0;
+    const BrickPlan &P = c->bplan[v];
+    const Level &L = c->lv[P.lm];
+    Timed t(c, (vel ? PS_COARSE_U64 : PS_COARSE_P64) + (sizeof(T) == 4 ? 2 : 0), P.lm, vel ? L.nu : L.np);
+    launch_bricks<T>(c->d.dim, v, level_table<T>(c), c->bplan_dev[v], P, ncyc, xzero ? 1 : 0, c->bctl, c->s);
+}
+
 template <typename T>
 void vcycle(ibb_ctx *c, bool vel, int l)
 {
+    if (c->bricks[vel ? 1 : 0] && !c->plain && l == c->bplan[vel ? 1 : 0].lm) {
+        brick_cycles<T>(c, vel, 1, l > 0);
+        return;
+    }
     Level &L = c->lv[l];
     const int D = c->d.dim;
     int vm[3];
@@ -982,13 +1241,46 @@ void vcycle(ibb_ctx *c, bool vel, int l)
     for (int s = 0; s < c->d.nu2; ++s) sweep<T>(c, vel, l);
 }
 
-// the reduced scalar back on the host
+// n V-cycles on level 0 from a zero iterate
+template <typename T>
+void vcycles_from_zero(ibb_ctx *c, bool vel, int n)
+{
+    if (c->bricks[vel ? 1 : 0] && !c->plain && c->bplan[vel ? 1 : 0].lm == 0) brick_cycles<T>(c, vel, n, true);
+    else
+        for (int it = 0; it < n; ++it) vcycle<T>(c, vel, 0);
+}
+
+// the reduced scalar back on the host; a launch of bricks that had to run on
+// one workgroup is the last (the device is shared with another process)
 ibb_status fetch_scalar(ibb_ctx *c, double *out)
 {
-    HIPCHK(hipMemcpyAsync(out, c->scalar, sizeof(double), hipMemcpyDeviceToHost, c->s));
+    struct {
+        double scalar;
+        BrickCtl ctl;
+    } h{};
+    HIPCHK(hipMemcpyAsync(&h, c->scalar, c->bctl ? sizeof(h) : sizeof(double), hipMemcpyDeviceToHost, c->s));
     HIPCHK(hipStreamSynchronize(c->s));
+    *out = h.scalar;
+    if (h.ctl.solo_runs && h.ctl.limit) c->apart = true;
     return IBB_OK;
 }
+
+// Solves in progress per device.  A launch of bricks needs the chip's
+// workgroups together, so an iteration uses bricks only while its context's
+// solve is the only one: a solve counts itself before it looks, and has
+// finished on the device before it counts itself out, so of two at least one
+// launches pass by pass.  (Two launches of bricks at once would each hold a
+// part of the chip until the time limit of their start; and small solves on
+// several streams share the chip better pass by pass.)
+std::atomic<int> solving[64];
+struct Solving {
+    std::atomic<int> &n;
+    explicit Solving(const ibb_ctx *c) : n(solving[c->dev & 63]) { n.fetch_add(1); }
+    ~Solving() { n.fetch_sub(1); }
+};
+void pass_by_pass(ibb_ctx *c) { c->plain = c->apart || solving[c->dev & 63].load() > 1; }
+// index of the graphs of the present choice
+int graph_set(const ibb_ctx *c, bool vel) { return c->plain && c->bricks[vel ? 1 : 0] ? 1 : 0; }
 
 ibb_status read_scalar(ibb_ctx *c, int nparts, double *out)
 {
@@ -1182,12 +1474,12 @@ void gcr_iteration_launches(ibb_ctx *c, bool vel, int j)
     if (!refined) {
         for (int a = 0; a < nc; ++a) launch_fill<double>(xl.c[a], L0.g.nel, 0.0, c->s);
         launch_load_unknowns<double>(L0.g, nc, masks, cview(g.r), bl, c->s);
-        vcycle<double>(c, vel, 0);
+        vcycles_from_zero<double>(c, vel, 1);
         launch_load_unknowns<double>(L0.g, nc, masks, cview(xl), z, c->s);
     } else {
         for (int a = 0; a < nc; ++a) launch_fill<float>(xl32.c[a], L0.g.nel, 0.0f, c->s);
         launch_cast_unknowns<double, float>(L0.g, nc, masks, cview(g.r), bl32, c->s);
-        for (int it = 0; it < c->d.inner_cycles; ++it) vcycle<float>(c, vel, 0);
+        vcycles_from_zero<float>(c, vel, c->d.inner_cycles);
         launch_add_correction(L0.g, nc, masks, cview(xl32), z, c->s);
     }
     // q = A z, then orthogonal to the stored q_i (modified Gram-Schmidt)
@@ -1274,7 +1566,7 @@ ibb_status gcr_launch(GcrRun &R)
         gcr_iteration_launches(c, vel, j);
         return IBB_OK;
     }
-    std::vector<hipGraphExec_t> &gt = c->gtick[vel ? 1 : 0];
+    std::vector<hipGraphExec_t> &gt = c->gtick[graph_set(c, vel)][vel ? 1 : 0];
     if ((int)gt.size() < c->d.krylov_restart) gt.assign(c->d.krylov_restart, nullptr);
     ibb_status st = ensure_graph(c, &gt[j], [&]() { gcr_iteration_launches(c, vel, j); });
     if (st) return st;
@@ -1318,9 +1610,11 @@ ibb_status solve_gcr(ibb_ctx *c, bool vel, int max_cycles, int exact, SolveOut *
     R.max_cycles = max_cycles;
     R.exact = exact;
     R.o = o;
+    Solving here(c);
     ibb_status st = gcr_begin(R);
     if (st) return st;
     while (gcr_more(R)) {
+        pass_by_pass(c);
         if ((st = gcr_launch(R))) return st;
         double s2;
         if ((st = fetch_scalar(c, &s2))) return st;
@@ -1334,6 +1628,7 @@ ibb_status solve_gcr(ibb_ctx *c, bool vel, int max_cycles, int exact, SolveOut *
 ibb_status solve(ibb_ctx *c, bool vel, int max_cycles, int exact, SolveOut *o)
 {
     if (c->d.krylov_restart > 0) return solve_gcr(c, vel, max_cycles, exact, o);
+    Solving here(c);
     const bool refined = c->d.precision == IBB_FP32_REFINED;
     const int D = c->d.dim;
     int vm[3];
@@ -1369,7 +1664,7 @@ ibb_status solve(ibb_ctx *c, bool vel, int max_cycles, int exact, SolveOut *o)
                                    VelArr<float>{{L0.bp32, nullptr, nullptr}},
                                    VelArr<float>{{L0.xp32, nullptr, nullptr}}, c->s);
         }
-        for (int it = 0; it < c->d.inner_cycles; ++it) vcycle<float>(c, vel, 0);
+        vcycles_from_zero<float>(c, vel, c->d.inner_cycles);
         Timed t(c, PS_OUTER, 0, units);
         if (vel)
             launch_add_correction(L0.g, D, vm, VelArrC<float>{{L0.xu32[0], L0.xu32[1], L0.xu32[2]}},
@@ -1381,21 +1676,20 @@ ibb_status solve(ibb_ctx *c, bool vel, int max_cycles, int exact, SolveOut *o)
     // Without kernel timing an iteration is one graph launch: the same
     // kernels in the same order as the launches below, so the same bits.
     const bool graph = !c->prof;
-    if (graph) {
-        st = ensure_graph(c, &c->tick[vel ? 1 : 0], [&]() {
-            one_iteration();
-            const int np = residual<double>(c, vel, 0, c->partial);
-            launch_reduce_final(c->partial, np, c->scalar, c->s);
-        });
-        if (st) return st;
-    }
     auto iterate = [&](double *r) -> ibb_status {
         o->vcycles += refined ? c->d.inner_cycles : 1;
+        pass_by_pass(c);
         if (!graph) {
             one_iteration();
             return resid_norm(c, vel, r);
         }
-        return replay_norm(c, c->tick[vel ? 1 : 0], r);
+        hipGraphExec_t &tick = c->tick[graph_set(c, vel)][vel ? 1 : 0];
+        const ibb_status gs = ensure_graph(c, &tick, [&]() {
+            one_iteration();
+            const int np = residual<double>(c, vel, 0, c->partial);
+            launch_reduce_final(c->partial, np, c->scalar, c->s);
+        });
+        return gs ? gs : replay_norm(c, tick, r);
     };
     if ((st = resid_norm(c, vel, &rn))) return st;
     double rel = rn / nb;
@@ -1796,6 +2090,7 @@ ibb_status ibb_create(const ibb_desc *desc, int64_t max_nodes, int64_t max_sprin
     char *base = reinterpret_cast<char *>(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
     carve(c, base, false);
     c->s = reinterpret_cast<hipStream_t>(stream);
+    (void)hipGetDevice(&c->dev);
     // zero the whole workspace
     const size_t used = need - 256;
     launch_fill<unsigned char>(reinterpret_cast<unsigned char *>(base), (long long)used, 0, c->s);
@@ -1902,6 +2197,107 @@ ibb_status ibb_create(const ibb_desc *desc, int64_t max_nodes, int64_t max_sprin
     return IBB_OK;
 }
 
+ibb_status ibb_solver_scratch_bytes(ibb_ctx *c, size_t *bytes)
+{
+    if (!c || !bytes) return IBB_EINVAL;
+    *bytes = carve_bricks(c, nullptr, true);
+    return IBB_OK;
+}
+
+ibb_status ibb_set_solver_scratch(ibb_ctx *c, void *scratch, size_t bytes)
+{
+    if (!c) return IBB_EINVAL;
+    const size_t need = carve_bricks(c, nullptr, true);
+    if (!need) return IBB_OK;
+    if (!scratch || c->bctl) return fail(c, IBB_EINVAL, "ibb_set_solver_scratch: no memory, or set before");
+    if (bytes < need) return fail(c, IBB_ENOMEM, "ibb_set_solver_scratch: fewer bytes than ibb_solver_scratch_bytes");
+    char *base = reinterpret_cast<char *>(((uintptr_t)scratch + 255) & ~(uintptr_t)255);
+    carve_bricks(c, base, false);
+    // bricks, if the chip holds all their workgroups at once (otherwise the
+    // levels are launched pass by pass): plans with the mailboxes' addresses,
+    // the control block
+    BrickCtl ctl{};
+    ctl.limit = BRICK_WAIT;
+    bool use[2];
+    for (int v = 0; v < 2; ++v) {
+        use[v] = c->planned[v] && c->tail[v].n > 0;
+        if (!use[v]) continue;
+        BrickPlan &P = c->bplan[v];
+        P.nu1 = c->d.nu1;
+        P.nu2 = c->d.nu2;
+        P.tail = c->tail[v];
+        P.L = c->L;
+        const int fit = c->d.precision == IBB_FP32_REFINED ? bricks_resident<float>(c->d.dim, v, P.lds_bytes)
+                                                            : bricks_resident<double>(c->d.dim, v, P.lds_bytes);
+        if (fit < P.nwg) {
+            use[v] = false;
+            continue;
+        }
+        for (int l = P.lm; l <= P.lc + 1; ++l) {
+            // the arrays as BrickLev states them
+            auto at_place = [&](const auto *first, const auto *p, int k) {
+                return reinterpret_cast<const char *>(p) - reinterpret_cast<const char *>(first) ==
+                       (ptrdiff_t)k * P.lev[l].stride;
+            };
+            const Level &Q = c->lv[l];
+            const int D = c->d.dim;
+            bool placed;
+            if (c->d.precision == IBB_FP32_REFINED)
+                placed = at_place(Q.xp32, Q.bp32, 1) && at_place(Q.xp32, Q.xu32[0], 3) &&
+                         at_place(Q.xp32, Q.rho32[D - 1], 6 + 5 * (D - 1)) && at_place(Q.xp32, Q.muc32, 3 + 5 * D) &&
+                         at_place(Q.xp32, Q.mue32[2], 4 + 5 * D + c->E - 1);
+            else
+                placed = at_place(Q.xp, Q.bp, 1) && at_place(Q.xp, Q.xu[0], 3) &&
+                         at_place(Q.xp, Q.rho[D - 1], 6 + 5 * (D - 1)) && at_place(Q.xp, Q.muc, 3 + 5 * D) &&
+                         at_place(Q.xp, Q.mue[2], 4 + 5 * D + c->E - 1);
+            if (!placed) use[v] = false;
+            P.lev[l].mx = c->bmx[l];
+            P.lev[l].mb = c->bmb[l];
+        }
+    }
+    launch_fill<unsigned char>(reinterpret_cast<unsigned char *>(base), (long long)(need - 256), 0, c->s);
+    BrickCtl *at_ctl = reinterpret_cast<BrickCtl *>(c->scalar + 1);
+    HIPCHK(hipMemcpyAsync(at_ctl, &ctl, sizeof(BrickCtl), hipMemcpyHostToDevice, c->s));
+    for (int v = 0; v < 2; ++v) {
+        if (!use[v]) continue;
+        HIPCHK(hipMemcpyAsync(c->bplan_dev[v], &c->bplan[v], sizeof(BrickPlan), hipMemcpyHostToDevice, c->s));
+        if (c->d.precision == IBB_FP32_REFINED)
+            launch_brick_tables<float>(c->d.dim, v, c->tab32, c->bplan_dev[v], c->bplan[v], c->s);
+        else
+            launch_brick_tables<double>(c->d.dim, v, c->tab64, c->bplan_dev[v], c->bplan[v], c->s);
+    }
+    HIPCHK(hipStreamSynchronize(c->s));
+    HIPCHK(hipGetLastError());
+    c->bctl = at_ctl;
+    // what was captured so far runs pass by pass
+    for (int v = 0; v < 2; ++v) {
+        if (!use[v]) continue;
+        c->bricks[v] = true;
+        std::swap(c->tick[0][v], c->tick[1][v]);
+        std::swap(c->gtick[0][v], c->gtick[1][v]);
+    }
+    return IBB_OK;
+}
+
+// Not part of the interface (tests): bricks of a context on or off (before
+// its first solve), the time limit of their start, and back the first brick
+// level per system (-1: none) and the launches that ran on one workgroup
+// (negative: workgroups that gave up waiting for a value).
+int ibmg_bricks_control(ibb_ctx *c, int on, long long limit, int first_level[2], int *solo_runs)
+{
+    for (int v = 0; v < 2; ++v) {
+        if (!on) c->bricks[v] = false;
+        if (first_level) first_level[v] = c->bricks[v] ? c->bplan[v].lm : -1;
+    }
+    if (!c->bctl) return 0;
+    if (hipStreamSynchronize(c->s) != hipSuccess) return 1;
+    BrickCtl ctl;
+    if (hipMemcpy(&ctl, c->bctl, sizeof(ctl), hipMemcpyDeviceToHost) != hipSuccess) return 1;
+    if (solo_runs) *solo_runs = ctl.lost ? -ctl.lost : ctl.solo_runs;
+    ctl.limit = limit < 0 ? BRICK_WAIT : limit;
+    return hipMemcpy(c->bctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice) == hipSuccess ? 0 : 1;
+}
+
 ibb_status ibb_destroy(ibb_ctx *c)
 {
     if (!c) return IBB_EINVAL;
@@ -1910,11 +2306,13 @@ ibb_status ibb_destroy(ibb_ctx *c)
         if (c->ev[i]) (void)hipEventDestroy(c->ev[i]);
     for (auto &e : c->pev)
         if (e) (void)hipEventDestroy(e);
-    for (auto &g : c->tick)
-        if (g) (void)hipGraphExecDestroy(g);
-    for (auto &v : c->gtick)
-        for (auto &g : v)
+    for (auto &t : c->tick)
+        for (auto &g : t)
             if (g) (void)hipGraphExecDestroy(g);
+    for (auto &t : c->gtick)
+        for (auto &v : t)
+            for (auto &g : v)
+                if (g) (void)hipGraphExecDestroy(g);
     if (c->cap) (void)hipStreamDestroy(c->cap);
     delete c;
     return IBB_OK;
@@ -2677,6 +3075,7 @@ struct SideJoin {
 ibb_status group_solve(ibb_group *g, bool vel, GroupSolve &R)
 {
     const int n = (int)g->m.size();
+    Solving here(g->m[0]);
     R.out.assign(n, SolveOut());
     R.nb.assign(n, 0.0);
     R.rel.assign(n, 0.0);
@@ -2764,6 +3163,7 @@ ibb_status group_solve(ibb_group *g, bool vel, GroupSolve &R)
             for (int i = 0; i < n; ++i) {
                 if (!ran[i]) continue;
                 ibb_ctx *c = g->m[i];
+                c->plain = true;   // beside the other members' solves
                 if ((st = gcr_launch(gr[i]))) return st;
                 GCHK(hipMemcpyAsync(g->norms + i, c->scalar, sizeof(double), hipMemcpyDeviceToDevice, c->s));
             }

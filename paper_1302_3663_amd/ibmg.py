@@ -85,6 +85,7 @@ class Context:
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
         nbytes = footprint_bytes(params, max_nodes, max_springs, precision, inner_cycles)
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        self.scratch = None   # of the context's own solves, from the first on
         self.ctx = ctypes.c_void_p()
         st = self.lib.ibb_create(ctypes.byref(self.desc), max_nodes, max_springs,
                                  ctypes.c_void_p(self.workspace.data_ptr()), nbytes,
@@ -96,6 +97,22 @@ class Context:
         self.n_edge = sum(edge_counts(params))
         self.eta = 0
         self.m = 0
+
+    def _solver_scratch(self):
+        """ibb_set_solver_scratch before the first solve of the context itself (not of its group), if the device
+        has the memory."""
+        if self.scratch is not None:
+            return
+        n = ctypes.c_size_t()
+        _chk(self.lib, self.lib.ibb_solver_scratch_bytes(self.ctx, ctypes.byref(n)), "ibb_solver_scratch_bytes")
+        try:
+            with torch.cuda.stream(self.stream):
+                self.scratch = torch.empty(n.value, dtype=torch.uint8, device=self.device)
+        except torch.cuda.OutOfMemoryError:
+            self.scratch = torch.empty(0, dtype=torch.uint8, device=self.device)
+        if self.scratch.numel():
+            _chk(self.lib, self.lib.ibb_set_solver_scratch(self.ctx, ctypes.c_void_p(self.scratch.data_ptr()),
+                                                           self.scratch.numel()), "ibb_set_solver_scratch")
 
     def close(self):
         if self.ctx:
@@ -165,6 +182,7 @@ class Context:
 
     def projection_step(self, check=True):
         s = L.SolveStats()
+        self._solver_scratch()
         st = self.lib.ibb_projection_step(self.ctx, ctypes.byref(s))
         if check:
             self._c(st, "ibb_projection_step")
@@ -200,6 +218,7 @@ class Context:
         x = x0.clone()
         cyc = ctypes.c_int()
         rel = ctypes.c_double()
+        self._solver_scratch()
         st = self.lib.ibb_mg_solve(self.ctx, which, _ptr(b), _ptr(x), max_cycles, exact, ctypes.byref(cyc),
                                    ctypes.byref(rel))
         if check:
