@@ -111,7 +111,7 @@ struct ibb_ctx {
     // so once the solver scratch is there); mailboxes per level and the
     // control block, shared by the two systems (their solves follow each
     // other on one stream)
-    bool planned[2] = {false, false}, bricks[2] = {false, false};
+    bool plans_made = false, planned[2] = {false, false}, bricks[2] = {false, false};
     BrickPlan bplan[2] = {};
     BrickPlan *bplan_dev[2] = {};
     unsigned long long *bmx[MAXLEV] = {}, *bmb[MAXLEV] = {};
@@ -475,10 +475,15 @@ size_t carve(ibb_ctx *c, char *base, bool dry)
     return cv.off + 256;
 }
 
+bool plan_bricks(const ibb_ctx *c, bool vel, BrickPlan &P);
+
 // the solver scratch: mailboxes, plans and tables of the bricks
 size_t carve_bricks(ibb_ctx *c, char *base, bool dry)
 {
     Carver cv{base, 0, dry};
+    if (!c->plans_made)
+        for (int v = 0; v < 2; ++v) c->planned[v] = plan_bricks(c, v == 1, c->bplan[v]);
+    c->plans_made = true;
     if (!c->planned[0] && !c->planned[1]) return 0;
     // a dry run leaves the context as it is: it may be running with them
     auto put = [&](auto *&at, auto *got) {
@@ -775,7 +780,6 @@ void setup_shapes(ibb_ctx *c, const ibb_desc *d, int64_t max_nodes, int64_t max_
         c->tail[v].n = (int)n;
         c->tail[v].level = lt;
     }
-    for (int v = 0; v < 2; ++v) c->planned[v] = plan_bricks(c, v == 1, c->bplan[v]);
     // z-blocked colour passes on every 3D level when asked for (measured
     // slower than the flat passes, so not the default)
     for (int l = 0; l < c->L; ++l) c->lv[l].zb = d->dim == 3 && d->smoother_zblock > 0 ? 1 : 0;

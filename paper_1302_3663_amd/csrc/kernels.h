@@ -59,6 +59,37 @@ __host__ __device__ inline bool box_colour_pos(const Box &b, int colour, int t, 
     return i < b.lo[0] + b.ext[0];
 }
 
+// ---------------------------------------------------------------------------
+// Rows by waves: a wave takes 64 neighbouring points of one row (j, k), so
+// that whatever depends on j and k alone -- the divisions of the index, the
+// rules at the ends of those axes, the addresses of the rows read -- is
+// scalar work done once a wave, not once a point.  For rows of ROW_MIN points
+// and more; on shorter ones too many lanes would idle, and the points are
+// numbered through (box_pos).
+// ---------------------------------------------------------------------------
+constexpr int ROW_MIN = 24;
+constexpr int ROW_WAVES = 4;   // of a workgroup
+
+inline bool rows_by_waves(const Box &b) { return b.ext[0] >= ROW_MIN; }
+inline unsigned row_blocks(const Box &b)
+{
+    const long long waves = (long long)((b.ext[0] + 63) / 64) * b.ext[1] * b.ext[2];
+    return (unsigned)((waves + ROW_WAVES - 1) / ROW_WAVES);
+}
+
+// point of this lane of workgroup b's wave; false: none
+__device__ inline bool row_pos(const Box &box, unsigned b, int &i, int &j, int &k)
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int chunks = (box.ext[0] + 63) >> 6, t = (int)b * ROW_WAVES + wave;
+    const int row = t / chunks, kk = row / box.ext[1];
+    j = __builtin_amdgcn_readfirstlane(box.lo[1] + (row - kk * box.ext[1]));
+    k = __builtin_amdgcn_readfirstlane(box.lo[2] + kk);
+    const int c = (t - row * chunks) * 64 + (int)(threadIdx.x & 63);
+    i = box.lo[0] + c;
+    return kk < box.ext[2] && c < box.ext[0];
+}
+
 // Division of 0 <= t < 2^31 by a fixed d >= 1 through one 64-bit multiply:
 // with 2^(l-1) < d <= 2^l and m = ceil(2^(31+l) / d), floor(t / d) equals
 // (t m) >> (31 + l) exactly (Granlund and Montgomery, "Division by invariant

@@ -25,25 +25,36 @@
 
 namespace ibmg {
 
-// ---------------------------------------------------------------------------
-// Workgroups go to the chip's 8 XCDs in turn (workgroup b to XCD b mod 8),
-// and each XCD has its own L2.  Renumbered so that each XCD works through one
-// contiguous range of the index space, the rows and planes that neighbouring
-// points share stay in one L2.  A bijection of [0, gridDim.x); remap = 0
-// keeps the hardware order.  Measured on the smoothers: 10% faster on arrays
-// of 4.4 M entries, 5-7% slower on 34.5 M, where a plane's reuse window no
-// longer fits an XCD's L2 and the shared last-level cache did better with
-// every XCD on neighbouring rows; hence the size limit below.
-// ---------------------------------------------------------------------------
 constexpr long long XCD_REMAP_MAX_NEL = 16ll << 20;
 
+// ---------------------------------------------------------------------------
+// Workgroups go to the chip's 8 XCDs in turn (workgroup b to XCD b mod 8),
+// and each XCD has its own L2.  Renumbered so that the rows and planes that
+// neighbouring points share stay in one L2 (a bijection of [0, gridDim.x)):
+// remap < 0 gives each XCD one contiguous range of the index space, while
+// remap > 0 deals out strips of so many workgroups, an eighth of a plane, so
+// that an XCD keeps its strip from plane to plane.  0 keeps the hardware
+// order.  Measured on the smoothers: ranges are 10% faster than the hardware
+// order on arrays of 4.4 M entries and 5-7% slower on 34.5 M, where the planes
+// a point reads no longer fit an XCD's L2; strips are 1-2% faster there.
+// ---------------------------------------------------------------------------
 __device__ inline unsigned xcd_block(int remap)
 {
     constexpr unsigned NXCD = 8;
     const unsigned nb = gridDim.x, b = blockIdx.x;
     if (!remap) return b;
+    if (remap > 0) {
+        const unsigned n = (unsigned)remap, round = NXCD * n, r = b / round, t = b - r * round;
+        return (r + 1) * round <= nb ? r * round + (t % NXCD) * n + t / NXCD : b;
+    }
     const unsigned q = nb / NXCD, r = nb % NXCD, x = b % NXCD;
     return x * q + (x < r ? x : r) + b / NXCD;
+}
+
+static int xcd_remap(const Grid &g, const Box &box, long long blocks)
+{
+    const long long planes = g.D == 3 ? box.ext[2] : box.ext[1];
+    return g.nel <= XCD_REMAP_MAX_NEL ? -1 : (int)std::max<long long>(1, (blocks / planes + 4) / 8);
 }
 
 // ---------------------------------------------------------------------------
@@ -583,10 +594,25 @@ __global__ void __launch_bounds__(256) k_resid_p(Grid g, Box box, const T *__res
     if (partial) block_sum_store(acc, partial, blockIdx.x);
 }
 
+template <typename T, int D, int A>
+__device__ inline T resid_u_at(const Grid &g, const VelArrC<T> &b, const VelArr<T> &x, const CoefU<T> &cf, T mass,
+                               T cvisc, const VelArr<T> &r, int i, int j, int k)
+{
+    const long long f = at(g, i, j, k);
+    const T bf = b.c[A][f];
+    T Ax, dg;
+    u_row<T, D, A>(g, x, cf, mass, cvisc, i, j, k, Ax, dg);
+    const T rv = bf - Ax;
+    if (r.c[A]) r.c[A][f] = rv;
+    return rv;
+}
+
+// component blockIdx.y, as k_resid_p
 template <typename T, int D>
 __global__ void __launch_bounds__(256) k_resid_u(Grid g, VelBox boxes, VelArrC<T> b, VelArr<T> x, CoefU<T> cf, T mass,
                                                  T cvisc, VelArr<T> r, double *partial)
 {
+    constexpr int A2 = D == 3 ? 2 : 1;
     const int a = blockIdx.y;
     const Box box = boxes.b[a];
     const int n = box.ext[0] * box.ext[1] * box.ext[2];
@@ -594,17 +620,52 @@ __global__ void __launch_bounds__(256) k_resid_u(Grid g, VelBox boxes, VelArrC<T
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
         int i, j, k;
         box_pos(box, t, i, j, k);
-        const long long f = at(g, i, j, k);
-        const T bf = b.c[a][f];
-        T Ax, dg;
-        if (a == 0) u_row<T, D, 0>(g, x, cf, mass, cvisc, i, j, k, Ax, dg);
-        else if (a == 1) u_row<T, D, 1>(g, x, cf, mass, cvisc, i, j, k, Ax, dg);
-        else u_row<T, D, (D == 3 ? 2 : 1)>(g, x, cf, mass, cvisc, i, j, k, Ax, dg);
-        const T rv = bf - Ax;
-        if (r.c[a]) r.c[a][f] = rv;
+        T rv;
+        if (a == 0) rv = resid_u_at<T, D, 0>(g, b, x, cf, mass, cvisc, r, i, j, k);
+        else if (a == 1) rv = resid_u_at<T, D, 1>(g, b, x, cf, mass, cvisc, r, i, j, k);
+        else rv = resid_u_at<T, D, A2>(g, b, x, cf, mass, cvisc, r, i, j, k);
         acc += (double)rv * (double)rv;
     }
     if (partial) block_sum_store(acc, partial, (long long)blockIdx.y * gridDim.x + blockIdx.x);
+}
+
+// The residual, rows by waves: `ncomp` components from blockIdx.y on, in turn,
+// so that what they share (the velocities, the viscosities) comes from the
+// caches.  `all` holds the rows of all of them.  NORM: all components and
+// their squared norms, rounds of gridDim.x blocks, partial sums per component
+// and block.  Numbered through in a grid-stride loop over one component
+// (k_resid_u), the divisions of the index and each component's own fetch of
+// what they share bound it: 1110 us at 256 x 256 x 512 in FP32 against 725, in
+// FP64 with norms 2080 against 1580; 98 against 61 at 128 x 128 x 256 in FP32.
+template <typename T, int D, bool NORM>
+__global__ void __launch_bounds__(256) k_resid_u_rows(Grid g, Box all, VelBox boxes, VelArrC<T> b, VelArr<T> x,
+                                                      CoefU<T> cf, T mass, T cvisc, VelArr<T> r, int ncomp, int remap,
+                                                      unsigned blocks, double *partial)
+{
+    constexpr int A2 = D == 3 ? 2 : 1;
+    const int a0 = NORM ? 0 : blockIdx.y, a1 = NORM ? D : a0 + ncomp;
+    double acc[3] = {0.0, 0.0, 0.0};
+    for (unsigned blk = xcd_block(remap); blk < blocks; blk += gridDim.x) {
+        int i, j, k;
+        if (row_pos(all, blk, i, j, k)) {
+            auto in = [&](const Box &q) {
+                return i >= q.lo[0] && i < q.lo[0] + q.ext[0] && j >= q.lo[1] && j < q.lo[1] + q.ext[1] &&
+                       k >= q.lo[2] && k < q.lo[2] + q.ext[2];
+            };
+            auto add = [&](int a, T v) {
+                if (NORM) acc[a] += (double)v * (double)v;
+            };
+            if (a0 == 0 && in(boxes.b[0])) add(0, resid_u_at<T, D, 0>(g, b, x, cf, mass, cvisc, r, i, j, k));
+            if (a0 <= 1 && a1 > 1 && in(boxes.b[1])) add(1, resid_u_at<T, D, 1>(g, b, x, cf, mass, cvisc, r, i, j, k));
+            if (D == 3 && a1 > 2 && in(boxes.b[2])) add(2, resid_u_at<T, D, A2>(g, b, x, cf, mass, cvisc, r, i, j, k));
+        }
+        if (!NORM) return;
+    }
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        block_sum_store(acc[a], partial, (long long)a * gridDim.x + blockIdx.x);
+        __syncthreads();
+    }
 }
 
 // sum of squares of a field over the unknowns of one or more lattices
@@ -676,6 +737,96 @@ __global__ void __launch_bounds__(256) k_prolong_add(Grid gc, Grid gf, VelBox bo
     const T v = xe + (T)prolong_any<T, D>(vmask, gc, role, coarse.c[comp], i, j, k);
     fine.c[comp][e] = v;
     write_images(gf, vmask, role, fine.c[comp], i, j, k, v);
+}
+
+// The same interpolation for large boxes: a wave walks a row, so the taps
+// along y and z are scalars and only boundary lanes look for ghost images.
+// Numbered through, the points are bound by the instructions of their taps:
+// 573 us at 256 x 256 x 512 in FP32 against 320 by rows, 80 against 58 at
+// 128 x 128 x 256.  (The restriction by rows took the same time: 334 and 329.)
+
+// a point that may have ghost images: within one of an end of its axis
+__device__ inline bool near_end(const Grid &g, int d, int q) { return q <= 1 || q >= g.n[d] - 1; }
+
+// the ghost images of point i of a row; `ends`: the row has some along y or z
+template <typename T>
+__device__ inline void row_images(const Grid &g, int vmask, int role, bool ends, T *x, int i, int j, int k, T v)
+{
+    if (ends) {
+        write_images(g, vmask, role, x, i, j, k, v);
+        return;
+    }
+    if (!near_end(g, 0, i)) return;
+    const AxisImages im = images_of(g, 0, vmask & 1, role, i);
+    if (im.s[0]) x[at(g, im.q[0], j, k)] = im.s[0] > 0 ? v : -v;
+    if (im.s[1]) x[at(g, im.q[1], j, k)] = im.s[1] > 0 ? v : -v;
+}
+
+// The taps of the coarse iterate are read where they lie: the ghost positions
+// hold what they stand for (every pass that writes an unknown writes its
+// images) and the fixed faces hold zero.
+template <typename T, int D, int VM>
+__device__ inline void prolong_row(const Grid &gc, const Grid &gf, const Box &box, int role,
+                                   const T *__restrict__ coarse, T *fine, int j, int k)
+{
+    int q1[2], q2[2], q0[2];
+    double w1[2], w2[2], w0[2];
+    if (prl_weights((VM >> 1) & 1, j, q1, w1) == 1) { q1[1] = q1[0]; w1[1] = 0.0; }
+    q2[0] = 0;
+    w2[0] = 1.0;
+    if (D == 3 && prl_weights((VM >> 2) & 1, k, q2, w2) == 1) { q2[1] = q2[0]; w2[1] = 0.0; }
+    const bool ends = near_end(gf, 1, j) || (D == 3 && near_end(gf, 2, k));
+    const T *__restrict__ row[D == 3 ? 2 : 1][2];
+#pragma unroll
+    for (int c = 0; c < (D == 3 ? 2 : 1); ++c)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) row[c][b] = coarse + at(gc, 0, q1[b], q2[c]);
+    T *const frow = fine + at(gf, 0, j, k);
+#pragma unroll 1
+    for (int i = box.lo[0] + (int)(threadIdx.x & 63); i < box.lo[0] + box.ext[0]; i += 64) {
+        if (prl_weights(VM & 1, i, q0, w0) == 1) { q0[1] = q0[0]; w0[1] = 0.0; }
+        const T xe = frow[i];
+        T v[D == 3 ? 2 : 1][2][2];
+#pragma unroll
+        for (int c = 0; c < (D == 3 ? 2 : 1); ++c)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int a = 0; a < 2; ++a) v[c][b][a] = row[c][b][q0[a]];
+        double s = 0.0;
+#pragma unroll
+        for (int c = 0; c < (D == 3 ? 2 : 1); ++c)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int a = 0; a < 2; ++a) s += w0[a] * w1[b] * w2[c] * (double)v[c][b][a];
+        const T x = xe + (T)s;
+        frow[i] = x;
+        row_images(gf, VM, role, ends, fine, i, j, k, x);
+    }
+}
+
+// this wave's row of the box; false: none
+__device__ inline bool wave_row(const Box &box, int &j, int &k)
+{
+    const int row = (int)xcd_block(-1) * ROW_WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int kk = row / box.ext[1];
+    j = __builtin_amdgcn_readfirstlane(box.lo[1] + (row - kk * box.ext[1]));
+    k = __builtin_amdgcn_readfirstlane(box.lo[2] + kk);
+    return kk < box.ext[2];
+}
+
+template <typename T, int D, bool VEL>
+__global__ void __launch_bounds__(256) k_prolong_rows(Grid gc, Grid gf, VelBox boxes, int role, VelArrC<T> coarse,
+                                                      VelArr<T> fine)
+{
+    const int a = VEL ? (int)blockIdx.y : 0;
+    int j, k;
+    if (!wave_row(boxes.b[a], j, k)) return;
+    if (!VEL) prolong_row<T, D, 0>(gc, gf, boxes.b[0], role, coarse.c[0], fine.c[0], j, k);
+    else if (a == 0) prolong_row<T, D, 1>(gc, gf, boxes.b[0], role, coarse.c[0], fine.c[0], j, k);
+    else if (a == 1) prolong_row<T, D, 2>(gc, gf, boxes.b[1], role, coarse.c[1], fine.c[1], j, k);
+    else if (D == 3) prolong_row<T, D, 4>(gc, gf, boxes.b[2], role, coarse.c[2], fine.c[2], j, k);
 }
 
 // ---------------------------------------------------------------------------
@@ -1347,7 +1498,7 @@ void launch_smooth_p(const Grid &g, const T *b, T *x, const CoefP<T> &cf, T cvis
                      nbands);
         return;
     }
-    const int remap = g.nel <= XCD_REMAP_MAX_NEL;
+    const int remap = xcd_remap(g, P, blocks_for(n));
     if (g.D == 3)
         launch_timed(k_smooth_p<T, 3>, dim3(blocks_for(n)), dim3(256), s, g, P, b, x, cf, cvisc, colour, remap);
     else
@@ -1371,7 +1522,7 @@ void launch_smooth_u(const Grid &g, int a, const T *b, const VelArr<T> &x, const
         return;
     }
     const dim3 grid(blocks_for(n)), blk(256);
-    const int remap = g.nel <= XCD_REMAP_MAX_NEL;
+    const int remap = xcd_remap(g, P, blocks_for(n));
     if (g.D == 3) {
         if (a == 0) launch_timed(k_smooth_u<T, 3, 0>, grid, blk, s, g, P, b, x, cf, mass, cvisc, colour, remap);
         else if (a == 1) launch_timed(k_smooth_u<T, 3, 1>, grid, blk, s, g, P, b, x, cf, mass, cvisc, colour, remap);
@@ -1397,7 +1548,7 @@ void launch_smooth_u_dec(const Grid &g, const VelArrC<T> &b, const VelArr<T> &x,
     }
     if (mx <= 0) return;
     const dim3 grid(blocks_for(mx), g.D), blk(256);
-    const int remap = g.nel <= XCD_REMAP_MAX_NEL;
+    const int remap = xcd_remap(g, parts.b[0], blocks_for(mx));
     if (g.D == 3) launch_timed(k_smooth_u_dec<T, 3>, grid, blk, s, g, parts, b, x, cf, mass, cvisc, colour, remap);
     else launch_timed(k_smooth_u_dec<T, 2>, grid, blk, s, g, parts, b, x, cf, mass, cvisc, colour, remap);
 }
@@ -1458,7 +1609,7 @@ void launch_smooth_zm(const Grid &g, int a, const VelArrC<T> &xin, const T *b, c
     const long long nb = (long long)((P.ext[0] + ZM_TX - 1) / ZM_TX) * ((P.ext[1] + ZM_TY - 1) / ZM_TY) *
                          ((P.ext[2] + cz - 1) / cz);
     const dim3 grid((unsigned)nb), blk(ZM_BS);
-    const int remap = 1;
+    const int remap = -1;
 #define ZM(AA) launch_timed(k_smooth_zm<T, AA>, grid, blk, s, g, P, xin, b, cu, mass, cvisc, xout, cz, remap)
     if (a == 0) ZM(0);
     else if (a == 1) ZM(1);
@@ -1485,6 +1636,12 @@ int launch_resid_p(const Grid &g, const T *b, const T *x, const CoefP<T> &cf, T 
     return (int)nb;
 }
 
+// From so many points a component on, the waves of one round of components
+// fill the chip several times over; below, each component has its own.  With
+// norms, rows by waves only from there on: below, the order of the sums is
+// that of the solves in groups.
+constexpr long long RESID_ALL_MIN = 1ll << 20;
+
 template <typename T>
 int launch_resid_u(const Grid &g, const VelArrC<T> &b, const VelArr<T> &x, const CoefU<T> &cf, T mass, T cvisc,
                    const VelArr<T> &r, double *partial, hipStream_t s)
@@ -1494,6 +1651,30 @@ int launch_resid_u(const Grid &g, const VelArrC<T> &b, const VelArr<T> &x, const
     for (int a = 0; a < 3; ++a) {
         parts.b[a] = a < g.D ? unk_box(g, face_mask(a)) : Box{{0, 0, 0}, {0, 0, 0}};
         if (a < g.D && box_count(parts.b[a]) > mx) mx = box_count(parts.b[a]);
+    }
+    const bool large = mx >= RESID_ALL_MIN;
+    if (rows_by_waves(parts.b[0]) && (large || !partial)) {
+        Box all = parts.b[0];
+        for (int a = 1; a < g.D; ++a)
+            for (int d = 0; d < 3; ++d) {
+                const int hi = std::max(all.lo[d] + all.ext[d], parts.b[a].lo[d] + parts.b[a].ext[d]);
+                all.lo[d] = std::min(all.lo[d], parts.b[a].lo[d]);
+                all.ext[d] = hi - all.lo[d];
+            }
+        const unsigned blocks = row_blocks(all), nb = partial ? std::min(blocks, NORM_BLOCKS_MAX) : blocks;
+        const dim3 grid(nb, large ? 1 : g.D), blk(256);
+        const int nc = large ? g.D : 1, remap = xcd_remap(g, all, blocks);
+#define LAUNCH(DD, NN) \
+    launch_timed(k_resid_u_rows<T, DD, NN>, grid, blk, s, g, all, parts, b, x, cf, mass, cvisc, r, nc, remap, blocks, partial)
+        if (g.D == 3) {
+            if (partial) LAUNCH(3, true);
+            else LAUNCH(3, false);
+        } else {
+            if (partial) LAUNCH(2, true);
+            else LAUNCH(2, false);
+        }
+#undef LAUNCH
+        return (int)nb * g.D;
     }
     const unsigned nb = stride_blocks(mx);
     if (g.D == 3)
@@ -1559,6 +1740,23 @@ void launch_restrict(const Grid &gf, const Grid &gc, int ncomp, const int *vmask
                      coarse, scale, zx);
 }
 
+// Interpolation by rows: of the pressure or of the velocity's components, from
+// 2^21 points a component on (at 64 x 64 x 128 and 96 x 96 x 192 in FP64 both
+// forms take the same time, 15.4 and 16.2 us), and rows that fill most of
+// their waves
+constexpr long long PROLONG_ROWS_MIN = 1ll << 21;
+
+static bool prolong_by_rows(const VelBox &parts, int ncomp, int masks, int role, long long points)
+{
+    bool rows = (role == ROLE_P && masks == 0) || (role == ROLE_V && masks == (ncomp == 3 ? 0x421 : 0x21));
+    for (int a = 0; a < ncomp; ++a) rows = rows && rows_by_waves(parts.b[a]);
+    return rows && points >= PROLONG_ROWS_MIN;
+}
+static unsigned wave_row_blocks(const Box &b)
+{
+    return (unsigned)(((long long)b.ext[1] * b.ext[2] + ROW_WAVES - 1) / ROW_WAVES);
+}
+
 template <typename T>
 void launch_prolong_add(const Grid &gc, const Grid &gf, int ncomp, const int *vmasks, int role,
                         const VelArrC<T> &coarse, const VelArr<T> &fine, hipStream_t s)
@@ -1576,6 +1774,21 @@ void launch_prolong_add(const Grid &gc, const Grid &gf, int ncomp, const int *vm
         }
     }
     if (mx <= 0) return;
+    if (prolong_by_rows(parts, ncomp, masks, role, mx)) {
+        unsigned nb = 1;
+        for (int a = 0; a < ncomp; ++a) nb = std::max(nb, wave_row_blocks(parts.b[a]));
+        const dim3 grid(nb, ncomp), blk(256);
+#define LAUNCH(DD, VV) launch_timed(k_prolong_rows<T, DD, VV>, grid, blk, s, gc, gf, parts, role, coarse, fine)
+        if (gf.D == 3) {
+            if (masks) LAUNCH(3, true);
+            else LAUNCH(3, false);
+        } else {
+            if (masks) LAUNCH(2, true);
+            else LAUNCH(2, false);
+        }
+#undef LAUNCH
+        return;
+    }
     if (gf.D == 3)
         launch_timed(k_prolong_add<T, 3>, dim3(blocks_for(mx), ncomp), dim3(256), s, gc, gf, parts, masks, role,
                      coarse, fine);
