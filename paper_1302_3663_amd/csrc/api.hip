@@ -1757,6 +1757,15 @@ void coarsest_tables(ibb_ctx *c, std::vector<long long> &ip, std::vector<int> &c
     for (int a = 0; a < c->d.dim; ++a) add(face_mask(a), a, iu, cu);
 }
 
+// Room for the table of a spread: the finest level's pressure right-hand side
+// and residual, which hold nothing between solves (carved one after the
+// other).
+NodeTab solver_node_table(ibb_ctx *c, double width, int eta)
+{
+    const Level &L0 = c->lv[0];
+    return node_table(L0.g, width, eta, L0.bp, (L0.rp - L0.bp) + L0.g.nel);
+}
+
 // spread, coarse coefficients, FP32 copies, coarsest inverses
 ibb_status rebuild_coefficients(ibb_ctx *c)
 {
@@ -1776,9 +1785,11 @@ ibb_status rebuild_coefficients(ibb_ctx *c)
     bins_for_width(d, d->omega, b.nb, b.bs);
     b.nbins = b.nb[0] * b.nb[1] * b.nb[2];
     launch_bin_nodes(L0.g, b, c->X, em, c->eta, c->scan_tmp, c->s);
+    const NodeTab tab = solver_node_table(c, d->omega, c->eta);
+    launch_node_table(L0.g, d->kernel, b, c->X, c->F, em, c->eta, d->omega, tab, c->s);
     for (int a = 0; a < D; ++a) {
         Timed t(c, PS_SPREAD_FACE, 0, lattice_count(L0.g, face_mask(a)));
-        launch_spread_face(L0.g, c->ph, b, c->X, c->F, em, a, d->omega, c->f[a], L0.rho[a], c->s);
+        launch_spread_face(L0.g, c->ph, b, tab, c->X, c->F, em, a, d->omega, c->f[a], L0.rho[a], c->s);
     }
     // with constant viscosity (eq:NSdis1) no row reads the viscosity fields,
     // which keep the fluid value they were created with
@@ -1786,11 +1797,11 @@ ibb_status rebuild_coefficients(ibb_ctx *c)
     if (visc) {
         {
             Timed t(c, PS_SPREAD_VISC, 0, lattice_count(L0.g, 0));
-            launch_spread_visc(L0.g, c->ph, b, c->X, em, 0, L0.muc, c->s);
+            launch_spread_visc(L0.g, c->ph, b, tab, c->X, em, 0, L0.muc, c->s);
         }
         for (int e = 0; e < c->E; ++e) {
             Timed t(c, PS_SPREAD_VISC, 0, lattice_count(L0.g, edge_mask(D, c->edge_axis[e])));
-            launch_spread_visc(L0.g, c->ph, b, c->X, em, edge_mask(D, c->edge_axis[e]), L0.mue[c->edge_axis[e]],
+            launch_spread_visc(L0.g, c->ph, b, tab, c->X, em, edge_mask(D, c->edge_axis[e]), L0.mue[c->edge_axis[e]],
                                c->s);
         }
     }
@@ -2629,8 +2640,10 @@ ibb_status ibb_spread(ibb_ctx *c, double width, int64_t n, const double *X, cons
     bins_for_width(&c->d, width, b.nb, b.bs);
     b.nbins = b.nb[0] * b.nb[1] * b.nb[2];
     launch_bin_nodes(L0.g, b, X, n > 0 ? n : 1, (int)n, c->scan_tmp, c->s);
+    const NodeTab tab = solver_node_table(c, width, (int)n);
+    launch_node_table(L0.g, c->d.kernel, b, X, F, n, (int)n, width, tab, c->s);
     for (int a = 0; a < c->d.dim; ++a)
-        launch_spread_face(L0.g, c->ph, b, X, F, n > 0 ? n : 1, a, width, L0.ru[a], nullptr, c->s);
+        launch_spread_face(L0.g, c->ph, b, tab, X, F, n > 0 ? n : 1, a, width, L0.ru[a], nullptr, c->s);
     faces_out(c, 0, L0.ru, out);
     HIPCHK(hipGetLastError());
     return IBB_OK;
@@ -2729,7 +2742,7 @@ ibb_status ibb_spread_static(const ibb_desc *desc, double width, int64_t n, cons
     launch_bin_nodes(g, b, X, n > 0 ? n : 1, (int)n, scan_tmp, s);
     long long off = 0;
     for (int a = 0; a < desc->dim; ++a) {
-        launch_spread_face(g, ph, b, X, F, n > 0 ? n : 1, a, width, stage, nullptr, s);
+        launch_spread_face(g, ph, b, NodeTab{nullptr, 0, 0}, X, F, n > 0 ? n : 1, a, width, stage, nullptr, s);
         launch_layout(g, face_mask(a), stage, out + off, false, s);
         off += lattice_count(g, face_mask(a));
     }

@@ -13,6 +13,9 @@
 
 namespace ibmg {
 
+// lattices of so many points and fewer are spread with a wave a point
+constexpr long long SPREAD_WAVE_MAX_POINTS = 65536;
+
 static inline unsigned nblk(long long n) { return (unsigned)((n + 255) / 256); }
 
 __device__ inline double domain_len(const Grid &g, int d) { return g.n[d] * g.h; }
@@ -318,6 +321,300 @@ __device__ inline void lattice_coord(const Grid &g, int vmask, int i, int j, int
     for (int d = 0; d < 3; ++d) x[d] = ((vmask >> d) & 1) ? q[d] * g.h : (q[d] + 0.5) * g.h;
 }
 
+// ---------------------------------------------------------------------------
+// Spread through a table of factors.  A node's delta is a product of one
+// factor per axis, and the (4 w / h)^D lattice points in its support share
+// them: a gather that works out each factor where it is used is bound by its
+// cosines, three in FP64 for every pair of point and node.  So the factors are
+// worked out once a node and lattice index (k_node_table), by the expressions
+// of delta_w, and the gathers multiply them in its order: the same bits.
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) k_node_table(Grid g, int kernel, Bins bins, const double *__restrict__ X,
+                                                    const double *__restrict__ F, long long stride, int eta,
+                                                    double width, NodeTab tab)
+{
+    // a lattice point's coordinate is rounded before a node's is taken off, as
+    // where points work out their own
+#pragma clang fp contract(off)
+    // a thread a node, lattice kind and axis
+    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int runs = 2 * g.D;
+    if (t >= (long long)eta * runs) return;
+    const int p = (int)(t / runs), q = (int)(t - (long long)p * runs), v = q / g.D, d = q - v * g.D;
+    const int s = bins.sorted[p], n = g.n[d];
+    double *rec = tab.rec + (long long)p * tab.record;
+    const double Xd = X[d * stride + s], inv_w = 1.0 / width;
+    double c = Xd;
+    if (g.bc[d] == AX_PERIODIC) c -= domain_len(g, d) * floor(c / domain_len(g, d));
+    // one index below the support; a node far outside reaches nothing
+    const double lo = floor((c - 2.0 * width) / g.h - (v ? 0.0 : 0.5));
+    const bool reach = lo > -1e9 && lo < 1e9;
+    const int base = reach ? (int)lo : -(1 << 30);
+    reinterpret_cast<int *>(rec)[v * 4 + d] = base;
+    if (v == 0 && F) rec[4 + d] = F[d * stride + s];
+    double *f = rec + 8 + (v * g.D + d) * tab.nt;
+    for (int e = 0; e < tab.nt; ++e) {
+        int i = base + e;
+        if (g.bc[d] == AX_PERIODIC) i = i < 0 ? i + n : (i >= n ? i - n : i);
+        const double x = v ? i * g.h : (i + 0.5) * g.h;
+        const double r = min_image(g, d, x - Xd) * inv_w;
+        f[e] = reach && fabs(r) < 2.0 ? phi_eval(kernel, r) : 0.0;
+    }
+}
+
+NodeTab node_table(const Grid &g, double width, int eta, double *at, long long room)
+{
+    NodeTab t{nullptr, 0, 0};
+    long long points = 1;
+    for (int d = 0; d < g.D; ++d) points *= stored_extent(g, d, 1);
+    const double nt = ceil(4.0 * width / g.h) + 2.0;
+    if (eta <= 0 || points <= SPREAD_WAVE_MAX_POINTS || nt > 64.0) return t;
+    // an index of a short periodic axis could lie in a run twice
+    for (int d = 0; d < g.D; ++d)
+        if (g.bc[d] == AX_PERIODIC && nt > g.n[d]) return t;
+    t.nt = (int)nt;
+    t.record = 8 + 2 * g.D * t.nt;
+    if ((long long)eta * t.record <= room) t.rec = at;
+    return t;
+}
+
+// A wave takes a box of 8 x 4 x 2 lattice points (8 x 8 in two dimensions) and
+// walks the nodes of all bins that any of them looks at, in the order of
+// bin_candidates, so that ranges, indices and records are scalar and the lanes
+// read the same few lines of a record's factors; nodes that reach none of the
+// points are passed over.  With a point to itself a lane walked fewer nodes,
+// but each lane its own: a load touched some 25 lines, and that bound the
+// gather.  256 x 256 x 512 points, 150000 nodes, width 2.6 h: 3.3-4.4 ms a
+// lattice with the factors worked out for every pair, 2.1-3.4 through the
+// table with a point a lane, 1.2-1.4 so; 128 x 128 x 256 points, 40000 nodes,
+// width 1.3 h: 361-534, 171-286 and 120-133 us.
+template <int D>
+struct BoxGather {
+    static constexpr int BX = 8, BY = D == 3 ? 4 : 8, BZ = D == 3 ? 2 : 1;
+    const int *start;
+    const double *rec;
+    int q[3], n[3], off[3], head[3], record, nt;
+    int nb[3], qlo[3], qhi[3], first[3], cnt[3], lo[2], hi[2], runs;
+    bool near;
+
+    // this wave's box and lane's point; false: no box
+    __device__ bool place(const Grid &g, int vmask, int i0, int j0, int k0, int &i, int &j, int &k)
+    {
+        const int lane = threadIdx.x & 63;
+        i = i0 + (lane & 7);
+        j = j0 + (lane >> 3) % BY;
+        k = k0 + (lane >> 3) / BY;
+        const int o[3] = {i0, j0, k0}, e[3] = {BX, BY, BZ};
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            qlo[d] = o[d];
+            qhi[d] = min(o[d] + e[d], stored_extent(g, d, (vmask >> d) & 1)) - 1;
+        }
+        q[0] = i;
+        q[1] = j;
+        q[2] = k;
+        return i <= qhi[0] && j <= qhi[1] && k <= qhi[2];
+    }
+    __device__ void bins_of(const Grid &g, const Bins &bins, const NodeTab &tab, int vmask, bool live)
+    {
+        start = bins.start;
+        rec = tab.rec;
+        record = tab.record;
+        nt = tab.nt;
+        int own = 0;
+        double x[3], xl[3], xh[3];
+        lattice_coord(g, vmask, q[0], q[1], q[2], x);
+        lattice_coord(g, vmask, qlo[0], qlo[1], qlo[2], xl);
+        lattice_coord(g, vmask, qhi[0], qhi[1], qhi[2], xh);
+#pragma unroll
+        for (int d = D - 1; d >= 0; --d) {
+            const int v = (vmask >> d) & 1;
+            const bool per = g.bc[d] == AX_PERIODIC;
+            nb[d] = bins.nb[d];
+            n[d] = per ? g.n[d] : 0;
+            head[d] = v * 4 + d;
+            off[d] = 8 + (v * D + d) * nt;
+            own = own * nb[d] + bin_coord(bins, d, x[d]);
+            const int b0 = __builtin_amdgcn_readfirstlane(bin_coord(bins, d, xl[d])) - BIN_REACH;
+            const int b1 = __builtin_amdgcn_readfirstlane(bin_coord(bins, d, xh[d])) + BIN_REACH;
+            if (per && b1 - b0 + 1 >= nb[d]) {
+                first[d] = 0;
+                cnt[d] = nb[d];
+            } else if (per) {
+                first[d] = b0 < 0 ? b0 + nb[d] : b0;
+                cnt[d] = b1 - b0 + 1;
+            } else {
+                first[d] = max(b0, 0);
+                cnt[d] = min(b1, nb[d] - 1) - first[d] + 1;
+            }
+        }
+        if (D == 2) {
+            first[2] = 0;
+            cnt[2] = 1;
+        }
+        // along x the bins are one run, or two where they wrap
+        const int last = first[0] + cnt[0] - 1;
+        runs = last >= nb[0] ? 2 : 1;
+        lo[0] = first[0];
+        hi[0] = min(last, nb[0] - 1);
+        lo[1] = 0;
+        hi[1] = last - nb[0];
+        near = __any(live && !(bins.near && !bins.near[own]));
+    }
+    // take(weight, record) for every node that reaches this lane's point.
+    // Lanes look up the rows' ranges, then nodes, 64 at a time; the factors of
+    // eight nodes are in flight together.
+    template <typename F>
+    __device__ void each(double scale, F take) const
+    {
+        constexpr int U = 8;
+        const int lane = threadIdx.x & 63, total = cnt[2] * cnt[1] * runs;
+        for (int t0 = 0; t0 < total; t0 += 64) {
+            int p0 = 0, len = 0;
+            if (t0 + lane < total) {
+                const int t = (t0 + lane) / runs, r = (t0 + lane) - t * runs, c = t / cnt[1], b = t - c * cnt[1];
+                int y = first[1] + b, z = D == 3 ? first[2] + c : 0;
+                if (y >= nb[1]) y -= nb[1];
+                if (D == 3 && z >= nb[2]) z -= nb[2];
+                const int row = (z * nb[1] + y) * nb[0];
+                p0 = start[row + (r ? lo[1] : lo[0])];
+                len = start[row + (r ? hi[1] : hi[0]) + 1] - p0;
+            }
+            int sum = len;   // over the rows up to this one
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int s = __shfl_up(sum, o);
+                sum += lane >= o ? s : 0;
+            }
+            const int all = __builtin_amdgcn_readlane(sum, 63);
+            const int shift = p0 - (sum - len);   // place of a node less its number here
+            for (int base = 0; base < all; base += 64) {
+                const int num = base + lane;
+                int row = 0;   // first row whose sum exceeds num
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) row += __shfl(sum, row + o - 1) <= num ? o : 0;
+                const int at_row = __shfl(shift, row & 63), p = num < all ? num + at_row : 0;
+                const int *__restrict__ hdr = reinterpret_cast<const int *>(rec + (long long)p * record);
+                int h[D];
+                bool reach = num < all;
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    h[d] = hdr[head[d]];
+                    reach = reach && (n[d] || (h[d] <= qhi[d] && h[d] + nt > qlo[d]));
+                }
+                unsigned long long mask = __ballot(reach);
+                while (mask) {
+                    const double *at[U];
+                    double f[U][D];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        bool in = mask != 0;
+                        const int l = in ? __builtin_ctzll(mask) : 0;
+                        mask &= mask - 1;   // 0 stays 0
+                        at[u] = rec + (long long)__builtin_amdgcn_readlane(p, l) * record;
+                        int e[D];
+#pragma unroll
+                        for (int d = 0; d < D; ++d) {
+                            e[d] = q[d] - __builtin_amdgcn_readlane(h[d], l);
+                            if (n[d]) e[d] = e[d] < 0 ? e[d] + n[d] : (e[d] >= n[d] ? e[d] - n[d] : e[d]);
+                            in = in && (unsigned)e[d] < (unsigned)nt;
+                        }
+#pragma unroll
+                        for (int d = 0; d < D; ++d) f[u][d] = at[u][off[d] + (in ? e[d] : 0)];
+                        f[u][0] = in ? f[u][0] : 0.0;
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        double w = scale;
+#pragma unroll
+                        for (int d = 0; d < D; ++d) w *= f[u][d];
+                        if (w != 0.0) take(w, at[u]);
+                    }
+                }
+            }
+        }
+    }
+};
+
+// this wave's box of a lattice: four along x to a workgroup
+template <int D>
+__device__ inline bool wave_box(const Grid &g, int vmask, BoxGather<D> &nodes, int &i, int &j, int &k)
+{
+    using B = BoxGather<D>;
+    const int ny = (stored_extent(g, 1, (vmask >> 1) & 1) + B::BY - 1) / B::BY;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int nx = (stored_extent(g, 0, vmask & 1) + 4 * B::BX - 1) / (4 * B::BX);
+    const int t = blockIdx.x / nx, z = t / ny;
+    const int i0 = ((blockIdx.x - t * nx) * 4 + wave) * B::BX, j0 = (t - z * ny) * B::BY, k0 = z * B::BZ;
+    return nodes.place(g, vmask, i0, j0, k0, i, j, k);
+}
+template <int D>
+static unsigned wave_boxes(const Grid &g, int vmask)
+{
+    using B = BoxGather<D>;
+    const long long nx = (stored_extent(g, 0, vmask & 1) + 4 * B::BX - 1) / (4 * B::BX);
+    const long long ny = (stored_extent(g, 1, (vmask >> 1) & 1) + B::BY - 1) / B::BY;
+    return (unsigned)(nx * ny * ((stored_extent(g, 2, (vmask >> 2) & 1) + B::BZ - 1) / B::BZ));
+}
+
+template <int D>
+__global__ void __launch_bounds__(256) k_spread_face_t(Grid g, Phys ph, Bins bins, NodeTab tab, int has_f, int a,
+                                                       double width, double *f_out, double *rho_out)
+{
+    const int vmask = face_mask(a);
+    int i, j, k;
+    BoxGather<D> nodes;
+    const bool live = wave_box<D>(g, vmask, nodes, i, j, k);
+    if (!__any(live)) return;
+    double scale = 1.0;
+    for (int d = 0; d < D; ++d) scale /= width;
+    double accf = 0.0, accw = 0.0;
+    nodes.bins_of(g, bins, tab, vmask, live);
+    if (nodes.near)
+        nodes.each(scale, [&](double w, const double *r) {
+            if (has_f) accf += r[4 + a] * w;
+            accw += w;
+        });
+    if (!live) return;
+    const long long u = at(g, i, j, k);
+    if (f_out) f_out[u] = accf;
+    if (rho_out) rho_out[u] = ph.rho0 + ph.rho_b * ph.d0_pow_d * accw;
+}
+
+template <int D>
+__global__ void __launch_bounds__(256) k_spread_visc_t(Grid g, Phys ph, Bins bins, NodeTab tab, int vmask,
+                                                       double *mu_out)
+{
+    int i, j, k;
+    BoxGather<D> nodes;
+    const bool live = wave_box<D>(g, vmask, nodes, i, j, k);
+    if (!__any(live)) return;
+    const double width = ph.omega;
+    double scale = 1.0, vol = 1.0;
+    for (int d = 0; d < D; ++d) {
+        scale /= width;
+        vol *= 2.0 * width;
+    }
+    const double dmu = ph.mu_max - ph.mu_out;
+    double best = ph.mu_out, wmax = 0.0;
+    nodes.bins_of(g, bins, tab, vmask, live);
+    if (dmu > 0.0 && nodes.near)
+        nodes.each(scale, [&](double w, const double *) { wmax = w > wmax ? w : wmax; });
+    if (wmax > 0.0) {
+        const double cand = vol * dmu * wmax + ph.mu_out;
+        best = cand > best ? cand : best;
+    }
+    if (live) mu_out[at(g, i, j, k)] = best;
+}
+
+void launch_node_table(const Grid &g, int kernel, const Bins &bins, const double *X, const double *F, long long stride,
+                       int eta, double width, const NodeTab &tab, hipStream_t s)
+{
+    if (!tab.rec) return;
+    launch_timed(k_node_table, dim3(nblk((long long)eta * 2 * g.D)), dim3(256), s, g, kernel, bins, X, F, stride, eta,
+                 width, tab);
+}
+
 // f_a(x) = sum_s F_a(s) delta~ and rho_a(x) = rho0 + rho_b d0^D sum_s delta~
 // at every closed-domain a-face
 __global__ void __launch_bounds__(256) k_spread_face(Grid g, Phys ph, Bins bins, const double *__restrict__ X,
@@ -366,8 +663,6 @@ __global__ void __launch_bounds__(256) k_spread_face(Grid g, Phys ph, Bins bins,
 // the weights of 64 consecutive candidates at once; the sums then take them
 // in candidate order, through the same expressions as k_spread_face, so
 // the result is the same bits.
-constexpr long long SPREAD_WAVE_MAX_POINTS = 65536;
-
 __global__ void __launch_bounds__(256) k_spread_face_w(Grid g, Phys ph, Bins bins, const double *__restrict__ X,
                                                        const double *__restrict__ F, long long stride, int a,
                                                        double width, double *f_out, double *rho_out)
@@ -421,14 +716,21 @@ __global__ void __launch_bounds__(256) k_spread_face_w(Grid g, Phys ph, Bins bin
     }
 }
 
-void launch_spread_face(const Grid &g, const Phys &ph, const Bins &bins, const double *X, const double *F,
-                        long long stride, int a, double width, double *f_out, double *rho_out, hipStream_t s)
+void launch_spread_face(const Grid &g, const Phys &ph, const Bins &bins, const NodeTab &tab, const double *X,
+                        const double *F, long long stride, int a, double width, double *f_out, double *rho_out,
+                        hipStream_t s)
 {
     long long n = 1;
     for (int d = 0; d < 3; ++d) n *= stored_extent(g, d, d == a);
     if (n <= SPREAD_WAVE_MAX_POINTS)
         launch_timed(k_spread_face_w, dim3((unsigned)((n + 3) / 4)), dim3(256), s, g, ph, bins, X, F, stride, a,
                      width, f_out, rho_out);
+    else if (tab.rec && g.D == 3)
+        launch_timed(k_spread_face_t<3>, dim3(wave_boxes<3>(g, face_mask(a))), dim3(256), s, g, ph, bins, tab, F ? 1 : 0, a, width, f_out,
+                     rho_out);
+    else if (tab.rec)
+        launch_timed(k_spread_face_t<2>, dim3(wave_boxes<2>(g, face_mask(a))), dim3(256), s, g, ph, bins, tab, F ? 1 : 0, a, width, f_out,
+                     rho_out);
     else
         launch_timed(k_spread_face, dim3(nblk(n)), dim3(256), s, g, ph, bins, X, F, stride, a, width, f_out,
                      rho_out);
@@ -533,14 +835,18 @@ __global__ void __launch_bounds__(256) k_spread_visc_w(Grid g, Phys ph, Bins bin
     if (lane == 0) mu_out[at(g, i, j, k)] = best;
 }
 
-void launch_spread_visc(const Grid &g, const Phys &ph, const Bins &bins, const double *X, long long stride, int vmask,
-                        double *mu_out, hipStream_t s)
+void launch_spread_visc(const Grid &g, const Phys &ph, const Bins &bins, const NodeTab &tab, const double *X,
+                        long long stride, int vmask, double *mu_out, hipStream_t s)
 {
     long long n = 1;
     for (int d = 0; d < 3; ++d) n *= stored_extent(g, d, (vmask >> d) & 1);
     if (n <= SPREAD_WAVE_MAX_POINTS)
         launch_timed(k_spread_visc_w, dim3((unsigned)((n + 3) / 4)), dim3(256), s, g, ph, bins, X, stride, vmask,
                      mu_out);
+    else if (tab.rec && g.D == 3)
+        launch_timed(k_spread_visc_t<3>, dim3(wave_boxes<3>(g, vmask)), dim3(256), s, g, ph, bins, tab, vmask, mu_out);
+    else if (tab.rec)
+        launch_timed(k_spread_visc_t<2>, dim3(wave_boxes<2>(g, vmask)), dim3(256), s, g, ph, bins, tab, vmask, mu_out);
     else
         launch_timed(k_spread_visc, dim3(nblk(n)), dim3(256), s, g, ph, bins, X, stride, vmask, mu_out);
 }

@@ -563,10 +563,26 @@ void launch_bin_nodes(const Grid &g, const Bins &bins, const double *X, long lon
                       hipStream_t s);
 // spread of the face force (F may be null) and density, or of the viscosity
 // max at cells and edges; kind: 0 faces (axis a), 1 cells, 2 edges (axis c)
-void launch_spread_face(const Grid &g, const Phys &ph, const Bins &bins, const double *X, const double *F,
-                        long long stride, int a, double width, double *f_out, double *rho_out, hipStream_t s);
-void launch_spread_visc(const Grid &g, const Phys &ph, const Bins &bins, const double *X, long long stride, int vmask,
-                        double *mu_out, hipStream_t s);
+// The factors of the nodes' deltas along each axis, at the cells (v = 0) and
+// faces (v = 1) around them, in the order of Bins::sorted: a record of
+// NodeTab::record doubles a node, the first index of each run of nt factors
+// (8 ints, v * 4 + axis), the node's vector of F (3, and one unused), then the
+// runs (v * D + axis).  None: rec is null.
+struct NodeTab {
+    double *rec;
+    int nt, record;
+};
+// the table for a width, if lattices of the grid are spread point by point
+// and `room` doubles hold it
+NodeTab node_table(const Grid &g, double width, int eta, double *at, long long room);
+void launch_node_table(const Grid &g, int kernel, const Bins &bins, const double *X, const double *F, long long stride,
+                       int eta, double width, const NodeTab &tab, hipStream_t s);
+// tab: of these bins, nodes and F, or none
+void launch_spread_face(const Grid &g, const Phys &ph, const Bins &bins, const NodeTab &tab, const double *X,
+                        const double *F, long long stride, int a, double width, double *f_out, double *rho_out,
+                        hipStream_t s);
+void launch_spread_visc(const Grid &g, const Phys &ph, const Bins &bins, const NodeTab &tab, const double *X,
+                        long long stride, int vmask, double *mu_out, hipStream_t s);
 void launch_interp(const Grid &g, int kernel, double width, const VelArrC<double> &u, const double *X,
                    long long xstride, int eta, double *U, long long ustride, hipStream_t s);
 void launch_euler(const Grid &g, double c, const double *U, double *X, long long stride, int eta, hipStream_t s);
