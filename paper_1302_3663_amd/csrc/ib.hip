@@ -914,10 +914,99 @@ __global__ void __launch_bounds__(INTERP_BLOCK) k_interp(Grid g, int kernel, dou
     if (threadIdx.x == 0) U[a * ustride + s] = red[0] * hD;
 }
 
+// The same sum with a wave to a node and component, when the support spans at
+// most INTERP_SPAN lattice indices along each axis: lane l works out the
+// factor and the array index of one lattice index of one axis, and the taps
+// take theirs from the lanes, in place of three cosines a tap and eight
+// barriers a node.  A lane holds the two partial sums that two threads of the
+// block hold, and they are added in the block's order: the same bits.
+// Measured with 40000 nodes in 128 x 128 x 256: 353 us by blocks, 116 by waves.
+constexpr int INTERP_SPAN = 16;
+
+__global__ void __launch_bounds__(256) k_interp_w(Grid g, int kernel, double width, VelArrC<double> u,
+                                                  const double *__restrict__ X, long long xstride, int eta, double *U,
+                                                  long long ustride)
+{
+    const int a = blockIdx.y, s = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (s >= eta) return;   // the whole wave
+    const int lane = threadIdx.x & 63;
+    const double inv_w = 1.0 / width;
+    double scale = 1.0, hD = 1.0;
+    for (int d = 0; d < g.D; ++d) {
+        scale /= width;
+        hD *= g.h;
+    }
+    const int vmask = face_mask(a);
+    int qlo[3], ext[3];
+    double Xs[3] = {0.0, 0.0, 0.0};
+    for (int d = 0; d < 3; ++d) {
+        qlo[d] = 0;
+        ext[d] = 1;
+        if (d >= g.D) continue;
+        Xs[d] = X[d * xstride + s];
+        const double off = ((vmask >> d) & 1) ? 0.0 : 0.5;
+        qlo[d] = (int)floor((Xs[d] - 2.0 * width) / g.h - off);
+        ext[d] = (int)ceil((Xs[d] + 2.0 * width) / g.h - off) - qlo[d] + 1;
+    }
+    // lane l: lattice index l % INTERP_SPAN of axis l / INTERP_SPAN
+    const int d0 = lane / INTERP_SPAN;
+    double f = 0.0;
+    int at0 = -1;   // index into the array, -1: not a tap
+    if (d0 < g.D) {
+        const int vert = (vmask >> d0) & 1;
+        const int q = (d0 == 0 ? qlo[0] : (d0 == 1 ? qlo[1] : qlo[2])) + lane % INTERP_SPAN;
+        double xc;
+        {
+#pragma clang fp contract(off)
+            xc = vert ? q * g.h : (q + 0.5) * g.h;
+        }
+        const double r = (xc - (d0 == 0 ? Xs[0] : (d0 == 1 ? Xs[1] : Xs[2]))) * inv_w;
+        if (fabs(r) < 2.0) {
+            const int n = g.n[d0];
+            const bool per = g.bc[d0] == AX_PERIODIC;
+            const int tq = per ? ((q % n) + n) % n : q;
+            if (per || (tq >= 0 && tq < stored_extent(g, d0, vert))) {
+                at0 = tq;
+                f = phi_eval(kernel, r);
+            }
+        }
+    } else if (d0 == 2) {
+        at0 = 0;   // two dimensions: no third axis
+        f = 1.0;
+    }
+    const int exy = ext[0] * ext[1], ntap = exy * ext[2];
+    double acc[2] = {0.0, 0.0};
+    for (int t0 = 0; t0 < ntap; t0 += 128)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int t = t0 + 64 * e + lane;
+            const int tz = t / exy, txy = t - tz * exy, ty = txy / ext[0], tx = txy - ty * ext[0];
+            const bool in = t < ntap;
+            const int lx = in ? tx : 0, ly = INTERP_SPAN + (in ? ty : 0), lz = 2 * INTERP_SPAN + (in ? tz : 0);
+            const int ix = __shfl(at0, lx), iy = __shfl(at0, ly), iz = __shfl(at0, lz);
+            const double fx = __shfl(f, lx), fy = __shfl(f, ly), fz = __shfl(f, lz);
+            if (in && ix >= 0 && iy >= 0 && iz >= 0) {
+                double w = scale * fx;
+                w *= fy;
+                if (g.D == 3) w *= fz;
+                acc[e] += u.c[a][at(g, ix, iy, iz)] * w;
+            }
+        }
+    double sum = acc[0] + acc[1];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o);
+    if (lane == 0) U[a * ustride + s] = sum * hD;
+}
+
 void launch_interp(const Grid &g, int kernel, double width, const VelArrC<double> &u, const double *X,
                    long long xstride, int eta, double *U, long long ustride, hipStream_t s)
 {
     if (eta <= 0) return;
+    if (4.0 * width / g.h + 3.0 <= INTERP_SPAN) {
+        launch_timed(k_interp_w, dim3((eta + 3) / 4, g.D), dim3(256), s, g, kernel, width, u, X, xstride, eta, U,
+                     ustride);
+        return;
+    }
     launch_timed(k_interp, dim3(eta, g.D), dim3(INTERP_BLOCK), s, g, kernel, width, u, X, xstride, eta, U,
                        ustride);
 }
