@@ -8,6 +8,8 @@
 // The spread runs as a gather: each lattice point visits the nodes of the
 // bins around it, in ascending node order within a bin, so the result does
 // not depend on thread timing and no atomics touch the fields.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -105,43 +107,55 @@ __global__ void k_scatter_keys(const int *__restrict__ keys, int n, const int *_
 }
 
 // order each bucket by id modulo `mod` (mod = 0: by id).  A one-wavefront
-// workgroup takes the buckets blockIdx.x, + gridDim.x, ...: it loads the
-// bucket's ids into LDS and writes every entry to its rank, the number of
-// entries with a smaller key (keys within a bucket are distinct).  A bucket
-// longer than the LDS tile is ordered by the first lane, by insertion.
+// workgroup takes `per` neighbouring buckets at a time: its lanes look up
+// their lengths together, and each bucket of two and more is loaded into LDS
+// and every entry written to its rank, the number of entries with a smaller
+// key (keys within a bucket are distinct).  A bucket longer than the LDS tile
+// is ordered by the first lane, by insertion.  Most of the bins of a domain
+// are empty: looked up one after the other, 2 M of them took 95 us, and take 28 so.
 constexpr int RANK_TILE = 1024;
-constexpr int RANK_GRID = 8192;
+constexpr int RANK_GRID = 8192, RANK_PER = 16;
 
-__global__ void __launch_bounds__(64) k_sort_buckets(const int *__restrict__ start, int nb, int *ids, int mod)
+__global__ void __launch_bounds__(64) k_sort_buckets(const int *__restrict__ start, int nb, int *ids, int mod, int per)
 {
     __shared__ int tile[RANK_TILE];
-    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
-        const int lo = start[b], hi = start[b + 1], n = hi - lo;
-        if (n < 2) continue;
-        if (n <= RANK_TILE) {
-            for (int q = threadIdx.x; q < n; q += blockDim.x) tile[q] = ids[lo + q];
-            __syncthreads();
-            for (int q = threadIdx.x; q < n; q += blockDim.x) {
-                const int v = tile[q];
-                const int kv = mod ? v % mod : v;
-                int rank = 0;
-                for (int r = 0; r < n; ++r) {
-                    const int w = tile[r];
-                    rank += (mod ? w % mod : w) < kv;
+    for (long long b0 = (long long)blockIdx.x * per; b0 < nb; b0 += (long long)gridDim.x * per) {
+        const int own = (int)b0 + (int)threadIdx.x;
+        int first = 0, len = 0;
+        if ((int)threadIdx.x < per && own < nb) {
+            first = start[own];
+            len = start[own + 1] - first;
+        }
+        unsigned long long mask = __ballot(len > 1);
+        while (mask) {
+            const int l = __builtin_ctzll(mask);
+            mask &= mask - 1;
+            const int lo = __builtin_amdgcn_readlane(first, l), n = __builtin_amdgcn_readlane(len, l), hi = lo + n;
+            if (n <= RANK_TILE) {
+                for (int q = threadIdx.x; q < n; q += blockDim.x) tile[q] = ids[lo + q];
+                __syncthreads();
+                for (int q = threadIdx.x; q < n; q += blockDim.x) {
+                    const int v = tile[q];
+                    const int kv = mod ? v % mod : v;
+                    int rank = 0;
+                    for (int r = 0; r < n; ++r) {
+                        const int w = tile[r];
+                        rank += (mod ? w % mod : w) < kv;
+                    }
+                    ids[lo + rank] = v;
                 }
-                ids[lo + rank] = v;
-            }
-            __syncthreads();
-        } else if (threadIdx.x == 0) {
-            for (int i = lo + 1; i < hi; ++i) {
-                const int v = ids[i];
-                const int kv = mod ? v % mod : v;
-                int j = i - 1;
-                while (j >= lo && (mod ? ids[j] % mod : ids[j]) > kv) {
-                    ids[j + 1] = ids[j];
-                    --j;
+                __syncthreads();
+            } else if (threadIdx.x == 0) {
+                for (int i = lo + 1; i < hi; ++i) {
+                    const int v = ids[i];
+                    const int kv = mod ? v % mod : v;
+                    int j = i - 1;
+                    while (j >= lo && (mod ? ids[j] % mod : ids[j]) > kv) {
+                        ids[j + 1] = ids[j];
+                        --j;
+                    }
+                    ids[j + 1] = v;
                 }
-                ids[j + 1] = v;
             }
         }
     }
@@ -158,8 +172,10 @@ void launch_bucket_sort(const int *keys, int n, int nbuckets, int *count, int *s
     hipLaunchKernelGGL(k_scan_apply, dim3(nt), dim3(SCAN_TILE), 0, s, count, nbuckets, scan_tmp, start);
     launch_fill<int>(count, nbuckets, 0, s);
     if (n > 0) hipLaunchKernelGGL(k_scatter_keys, dim3(nblk(n)), dim3(256), 0, s, keys, n, start, count, ids);
-    const unsigned ng = (unsigned)(nbuckets < RANK_GRID ? (nbuckets > 0 ? nbuckets : 1) : RANK_GRID);
-    launch_timed(k_sort_buckets, dim3(ng), dim3(64), s, start, nbuckets, ids, mod);
+    // buckets beyond the first RANK_GRID share workgroups, up to RANK_PER each
+    const int per = std::max(1, std::min(RANK_PER, nbuckets / RANK_GRID));
+    const long long ng = std::min<long long>(std::max(1, (nbuckets + per - 1) / per), RANK_GRID * 16);
+    launch_timed(k_sort_buckets, dim3((unsigned)ng), dim3(64), s, start, nbuckets, ids, mod, per);
 }
 
 // ---------------------------------------------------------------------------
@@ -242,23 +258,38 @@ __device__ inline XRuns x_runs(const int lst[BIN_SPAN], int cnt)
     return r;
 }
 
-// near[bin]: does any bin where the bin's points look hold a node?
-__global__ void __launch_bounds__(256) k_bin_near(Grid g, Bins bins)
+// near[bin]: does any bin where the bin's points look hold a node?  Marked from
+// the occupied bins into cleared flags: asked bin by bin, 2 M bins took 90 us,
+// so with 40000 nodes 14 and 5 for the clearing.
+__global__ void __launch_bounds__(256) k_bin_near(Grid g, Bins bins, int eta)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= bins.nbins) return;
-    const int b[3] = {t % bins.nb[0], (t / bins.nb[0]) % bins.nb[1], t / (bins.nb[0] * bins.nb[1])};
-    int lst[3][BIN_SPAN], cnt[3];
-    for (int d = 0; d < 3; ++d) cnt[d] = bin_candidates(g, bins, d, b[d], lst[d]);
-    const XRuns xr = x_runs(lst[0], cnt[0]);
-    unsigned char any = 0;
-    for (int c = 0; c < cnt[2]; ++c)
-        for (int bb = 0; bb < cnt[1]; ++bb) {
-            const int row = (lst[2][c] * bins.nb[1] + lst[1][bb]) * bins.nb[0];
-            for (int q = 0; q < xr.n; ++q)
-                if (bins.start[row + xr.hi[q] + 1] > bins.start[row + xr.lo[q]]) any = 1;
-        }
-    bins.near[t] = any;
+    // a thread a node and (y, z) offset; the first node of a bin marks for it
+    constexpr int ROWS = BIN_SPAN * BIN_SPAN;
+    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (long long)eta * ROWS) return;
+    const int p = (int)(t / ROWS), o = (int)(t - (long long)p * ROWS);
+    const int bin = bins.bin_of[bins.sorted[p]];
+    if (bins.start[bin] != p) return;
+    const int b[3] = {bin % bins.nb[0], (bin / bins.nb[0]) % bins.nb[1], bin / (bins.nb[0] * bins.nb[1])};
+    // the e-th bin along axis d that looks at bin b: the relation of
+    // bin_candidates goes both ways
+    auto looks = [&](int d, int e) -> int {
+        if (d >= g.D) return e == 0 ? 0 : -1;
+        const int nb = bins.nb[d];
+        const bool per = g.bc[d] == AX_PERIODIC;
+        if (per && nb <= 2 * BIN_REACH) return e < nb ? e : -1;
+        const int q = b[d] + e - BIN_REACH;
+        if (per) return q < 0 ? q + nb : (q >= nb ? q - nb : q);
+        return q >= 0 && q < nb ? q : -1;
+    };
+    const int y = looks(1, o % BIN_SPAN), z = looks(2, o / BIN_SPAN);
+    if (y < 0 || z < 0) return;
+    unsigned char *row = bins.near + (z * bins.nb[1] + y) * bins.nb[0];
+#pragma unroll
+    for (int e = 0; e < BIN_SPAN; ++e) {
+        const int x = looks(0, e);
+        if (x >= 0) row[x] = 1;
+    }
 }
 
 void launch_bin_nodes(const Grid &g, const Bins &bins, const double *X, long long stride, int eta, int *scan_tmp,
@@ -266,7 +297,12 @@ void launch_bin_nodes(const Grid &g, const Bins &bins, const double *X, long lon
 {
     if (eta > 0) hipLaunchKernelGGL(k_bin_of, dim3(nblk(eta)), dim3(256), 0, s, g, bins, X, stride, eta);
     launch_bucket_sort(bins.bin_of, eta, bins.nbins, bins.count, bins.start, bins.sorted, 0, scan_tmp, s);
-    if (bins.near) hipLaunchKernelGGL(k_bin_near, dim3(nblk(bins.nbins)), dim3(256), 0, s, g, bins);
+    if (bins.near) {
+        launch_fill<unsigned char>(bins.near, bins.nbins, 0, s);
+        if (eta > 0)
+            hipLaunchKernelGGL(k_bin_near, dim3(nblk((long long)eta * BIN_SPAN * BIN_SPAN)), dim3(256), 0, s, g, bins,
+                               eta);
+    }
 }
 
 // the bins where a point looks for nodes, along each axis, and its own bin
