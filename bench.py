@@ -55,8 +55,10 @@ SITES = {
     3: ("k_smooth_p<float>", 4), 4: ("k_resid_u<double>", 8), 5: ("k_resid_p<double>", 8),
     6: ("k_resid_u<float>", 4), 7: ("k_resid_p<float>", 4), 8: ("k_restrict<double>", 8),
     9: ("k_restrict<float>", 4), 10: ("k_prolong_add<double>", 8), 11: ("k_prolong_add<float>", 4),
-    12: ("k_coarse_vcycle<double, D, 1>", 8), 13: ("k_coarse_vcycle<double, D, 0>", 8),
-    14: ("k_coarse_vcycle<float, D, 1>", 4), 15: ("k_coarse_vcycle<float, D, 0>", 4),
+    # the lower levels of a V-cycle in one launch: as bricks where a context
+    # runs them (bricks.hip), in one workgroup (k_coarse_vcycle) elsewhere
+    12: ("k_bricks or k_coarse_vcycle<double, D, 1>", 8), 13: ("k_bricks or k_coarse_vcycle<double, D, 0>", 8),
+    14: ("k_bricks or k_coarse_vcycle<float, D, 1>", 4), 15: ("k_bricks or k_coarse_vcycle<float, D, 0>", 4),
     16: ("k_dense_apply", 8), 17: ("outer-loop passes (norms, casts, clears, corrections)", 8),
     18: ("GCR vector passes", 8), 19: ("k_smooth_u_dec<double>", 8), 20: ("k_smooth_u_dec<float>", 4),
     21: ("one-launch sweep (k_smooth_rb, k_smooth_zm)<double>", 8),
@@ -163,7 +165,7 @@ def site_launches(p, site, level):
     D = p["dim"]
     T = "float" if SITES[site][1] == 4 else "double"
     if site in (12, 13, 14, 15):
-        return [(f"k_coarse_vcycle<{T}, {D}, {1 if site in (12, 14) else 0}>", None)]
+        return [(f"{k}<{T}, {D}, {1 if site in (12, 14) else 0}>", None) for k in ("k_bricks", "k_coarse_vcycle")]
     out = []
     if site in (21, 22):
         # one launch per sweep: the z-marching velocity sweep (3D; tiles of
@@ -741,7 +743,7 @@ def main():
                 bytes_per_unit=words_per_unit(dom["site"], D) * SITES[dom["site"]][1],
                 device_ms_per_step=round(dom["ms_per_step"], 3), share_of_step_kernels=round(dom["share"], 4))
     if dom["site"] in (12, 13, 14, 15, 16):
-        roof["limited_by"] = "latency (one workgroup, barriers between passes)"
+        roof["limited_by"] = "latency (exchanges or barriers between passes)"
     rp = rocprof_average(p, dom["site"], dom["level"], args.workload)
     if rp:
         roof["rocprof_avg_launch_us"] = rp

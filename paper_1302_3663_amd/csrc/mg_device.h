@@ -380,26 +380,22 @@ struct AxisTaps {
     double w[4];
 };
 
-// RAW: an index past the end of a periodic axis stays as it is (the source is
-// a window that holds the wrapped points themselves); `dead` is the index a
-// fixed face's tap reads instead (any valid one, its weight is zero)
-template <int NT, bool RAW = false>
+template <int NT>
 __device__ inline void resolve_taps(const Grid &g, int d, int vert, int role, const int *raw, const double *wraw,
-                                    AxisTaps &t, int dead = 0)
+                                    AxisTaps &t)
 {
 #pragma unroll
     for (int a = 0; a < NT; ++a) {
         int q = raw[a], s = 1;
-        const bool live = (RAW && g.bc[d] == AX_PERIODIC) || resolve(g, d, vert, role, q, s);
-        t.q[a] = live ? q : dead;
+        const bool live = resolve(g, d, vert, role, q, s);
+        t.q[a] = live ? q : 0;
         t.w[a] = live ? (s > 0 ? wraw[a] : -wraw[a]) : 0.0;
     }
 }
 
-// Full weighting around coarse point (I, J, K) of the fine values src(i, j, k)
-// in two steps: along x on every fine line (restrict_line), then over the
-// lines (restrict_lines, of their sums line(j, k)).  The bricks take them
-// apart; the other passes take restrict_point.
+// The first step of full weighting: along x on one fine line src(i) around the
+// coarse index I.  The bricks send these sums to the workgroups that weight
+// the lines; the other passes take restrict_point, which adds in this order.
 template <int VX, typename SRC>
 __device__ inline double restrict_line(const Grid &gf, int role, int I, SRC src)
 {
@@ -415,37 +411,6 @@ __device__ inline double restrict_line(const Grid &gf, int role, int I, SRC src)
 #pragma unroll
     for (int a = 0; a < N0; ++a) rs += t.w[a] * v[a];
     return rs;
-}
-
-// RAW, dead: as for resolve_taps
-template <int D, int VM, bool RAW, typename LINE>
-__device__ inline double restrict_lines(const Grid &gf, int role, int J, int K, LINE line, int dead1 = 0, int dead2 = 0)
-{
-    constexpr int N1 = (VM & 2) ? 3 : 4;
-    constexpr int N2 = D == 3 ? ((VM & 4) ? 3 : 4) : 1;
-    AxisTaps t1, t2;
-    int raw[4];
-    double wr[4];
-    rst_weights((VM >> 1) & 1, J, raw, wr);
-    resolve_taps<N1, RAW>(gf, 1, (VM >> 1) & 1, role, raw, wr, t1, dead1);
-    if (D == 3) {
-        rst_weights((VM >> 2) & 1, K, raw, wr);
-        resolve_taps<N2, RAW>(gf, 2, (VM >> 2) & 1, role, raw, wr, t2, dead2);
-    } else {
-        t2.q[0] = 0;
-        t2.w[0] = 1.0;
-    }
-    double v[N2][N1];
-#pragma unroll
-    for (int c = 0; c < N2; ++c)
-#pragma unroll
-        for (int b = 0; b < N1; ++b) v[c][b] = line(t1.q[b], t2.q[c]);
-    double s = 0.0;
-#pragma unroll
-    for (int c = 0; c < N2; ++c)
-#pragma unroll
-        for (int b = 0; b < N1; ++b) s += t1.w[b] * t2.w[c] * v[c][b];
-    return s;
 }
 
 // both steps at once, every load before the first sum (the same sums)
@@ -490,11 +455,9 @@ __device__ inline double restrict_point(const Grid &gf, int role, const T *__res
     return s;
 }
 
-// Linear interpolation at fine point (i, j, k) of the coarse values
-// src(I, J, K); RAW, dead as above.
-template <typename T, int D, int VM, bool RAW, typename SRC>
-__device__ inline double prolong_from(const Grid &gc, int role, SRC src, int i, int j, int k, int dead1 = 0,
-                                      int dead2 = 0)
+// linear interpolation of the coarse values src at fine point (i, j, k)
+template <typename T, int D, int VM>
+__device__ inline double prolong_point(const Grid &gc, int role, const T *__restrict__ src, int i, int j, int k)
 {
     constexpr int N2 = D == 3 ? 2 : 1;
     const int q[3] = {i, j, k};
@@ -506,8 +469,7 @@ __device__ inline double prolong_from(const Grid &gc, int role, SRC src, int i, 
         const int vert = (VM >> d) & 1;
         const int n = prl_weights(vert, q[d], raw, wr);
         if (n == 1) { raw[1] = raw[0]; wr[1] = 0.0; }
-        if (d == 0) resolve_taps<2>(gc, d, vert, role, raw, wr, t[d]);
-        else resolve_taps<2, RAW>(gc, d, vert, role, raw, wr, t[d], d == 1 ? dead1 : dead2);
+        resolve_taps<2>(gc, d, vert, role, raw, wr, t[d]);
     }
     if (D == 2) {
         t[2].q[0] = 0;
@@ -519,7 +481,7 @@ __device__ inline double prolong_from(const Grid &gc, int role, SRC src, int i, 
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int a = 0; a < 2; ++a) v[c][b][a] = src(t[0].q[a], t[1].q[b], t[2].q[c]);
+            for (int a = 0; a < 2; ++a) v[c][b][a] = src[at(gc, t[0].q[a], t[1].q[b], t[2].q[c])];
     double s = 0.0;
 #pragma unroll
     for (int c = 0; c < N2; ++c)
@@ -528,13 +490,6 @@ __device__ inline double prolong_from(const Grid &gc, int role, SRC src, int i, 
 #pragma unroll
             for (int a = 0; a < 2; ++a) s += t[0].w[a] * t[1].w[b] * t[2].w[c] * (double)v[c][b][a];
     return s;
-}
-
-template <typename T, int D, int VM>
-__device__ inline double prolong_point(const Grid &gc, int role, const T *__restrict__ src, int i, int j, int k)
-{
-    return prolong_from<T, D, VM, false>(
-        gc, role, [&](int a, int b, int c) { return src[at(gc, a, b, c)]; }, i, j, k);
 }
 
 template <typename T, int D>
