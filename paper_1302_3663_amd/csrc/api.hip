@@ -493,11 +493,13 @@ size_t carve_bricks(ibb_ctx *c, char *base, bool dry)
     const bool refined = c->d.precision == IBB_FP32_REFINED;
     const size_t words = (size_t)brick_mail_words(refined ? 4 : 8);
     for (int l = 0; l < c->L; ++l) {
-        bool used = false;
-        for (int v = 0; v < 2; ++v)
+        bool used = false, tail = false;
+        for (int v = 0; v < 2; ++v) {
             used = used || (c->planned[v] && l >= c->bplan[v].lm && l <= c->bplan[v].lc + 1);
+            tail = tail || (c->planned[v] && l == c->bplan[v].lc + 1);
+        }
         if (!used) continue;
-        put(c->bmx[l], cv.take<unsigned long long>((size_t)D * c->lv[l].g.nel * words));
+        put(c->bmx[l], cv.take<unsigned long long>((tail ? BRICK_TAIL_COPIES : 1) * (size_t)D * c->lv[l].g.nel * words));
         put(c->bmb[l], cv.take<unsigned long long>((size_t)D * c->lv[l].g.nel * words));
     }
     for (int v = 0; v < 2; ++v) {

@@ -13,6 +13,12 @@ constexpr int BRICK_THREADS = 512;
 constexpr int BRICK_SLOTS = 3;
 // workgroups at most (one per CU of the chip)
 constexpr int BRICK_MAX_WG = 256;
+// The tail level's right-hand side goes to every workgroup with rows of the
+// tail's matrix: BRICK_TAIL_ROWS at a time, dealt out in turn to those with a
+// box on that level.  The others do not read it.  Its mailbox has two copies,
+// used in turn by the cycles of a launch.
+constexpr int BRICK_TAIL_ROWS = BRICK_THREADS / TAIL_LANES, BRICK_TAIL_COPIES = 2;
+__host__ __device__ constexpr bool brick_has_rows(int wg, int n) { return wg * BRICK_TAIL_ROWS < n; }
 
 // What a pass over one component of a level (velocity component, or the
 // pressure) is made of, as uniform offsets: so one piece of code serves every
@@ -38,7 +44,8 @@ struct BrickPass {
 // cz = 1), sy x sz of them, each in a window one line wider on every side, of
 // wy lines a plane (the largest box's) and wn entries per component, at byte
 // lds of the workgroup's LDS.  mx, mb: mailboxes, one uniform array of entries
-// (brick_mail_words 8-byte words each) per component.  The level's arrays lie
+// (brick_mail_words 8-byte words each) per component (the tail level's mx:
+// BRICK_TAIL_COPIES of them).  The level's arrays lie
 // `stride` bytes apart, in the order xp, bp, rp; then per component xu, bu,
 // ru, rho, beta; muc; the edge viscosities.
 struct BrickLev {

@@ -22,7 +22,12 @@
 // a neighbour, since it needs the neighbour's values of the passes between;
 // mb carries residuals, prolonged iterates and final iterates of a level
 // visit, any two of which are separated by exchanges that depend on the
-// readers of the first.
+// readers of the first.  The right-hand side of the tail's level is read whole
+// by every workgroup with rows of the tail's matrix, while a poster waits only
+// for the rows that it needs itself.  So it may be a cycle ahead of a reader,
+// but not two: no row is posted before every workgroup of that level has
+// posted its part of the same cycle, each after it has read the cycle before.
+// That mailbox has two copies, used in turn.
 //
 // All workgroups must be on the chip at once.  Each first counts itself in;
 // if the last has not arrived within a time limit (workgroups of another
@@ -700,10 +705,10 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_brick_tables(const LevTab<T> 
 // Second step of the restriction: components [c0, c0 + nc) of the coarse
 // right-hand side at the own points of the coarse brick C, from the x sums of
 // the lines around them in `buf`: into C's global b, or (last: C is the
-// tail's level) into its mx.
+// tail's level) into tail_mx, the cycle's copy of its mx.
 template <typename T, int D, int VEL>
 BRICK_FN void brick_restrict(const Brick<T, D, VEL> &C, const double *buf, int c0, int nc, const WindowAt &wa, int W,
-                             bool last, unsigned ep)
+                             bool last, u64 *tail_mx, unsigned ep)
 {
     each_own<T, D, VEL>(C, c0, nc, [&](int a, int s, int, int J, int K, int I) {
         // three lines per axis of faces, four per axis of cells (the fourth
@@ -738,7 +743,7 @@ BRICK_FN void brick_restrict(const Brick<T, D, VEL> &C, const double *buf, int c
         }
         const int e = (int)at(C.g, I, J, K);
         const BrickPass *P = &C.b->pass[a];
-        if (last) post<T>(C.mx0 + (P->mail + (unsigned)e * MW<T>), (T)sum, ep);
+        if (last) post<T>(tail_mx + (P->mail + (unsigned)e * MW<T>), (T)sum, ep);
         else C.arr((unsigned)e * (unsigned)sizeof(T) + P->coef[0]) = (T)sum;
     });
 }
@@ -994,6 +999,9 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_bricks(const LevTab<T> *__res
             ++ep;
             const bool coarse = has_box(&plan->lev[l + 1], wg);
             const int gs = cload(&plan->lev[l].gs);
+            // the tail level's right-hand side, in the cycle's copy
+            const unsigned ms = (unsigned)cload(&tab[l + 1].g.nel) * MW<T>;
+            u64 *const tail_mx = cload(&plan->lev[l + 1].mx) + (unsigned)(v / (2 * nl) % BRICK_TAIL_COPIES) * (NC * ms);
             if (act) {
                 fetch<T, D, VEL>(B, S, pd, dead);
                 __syncthreads();
@@ -1027,7 +1035,7 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_bricks(const LevTab<T> *__res
                 fetch_window<double>(cload(&C.b->from_s) + (size_t)wg * cload(&C.b->ns) + c0 * one, gs * one, B.mb0, ep,
                                      buf, dead);
                 __syncthreads();
-                brick_restrict<T, D, VEL>(C, buf, c0, gs, wa, W, last, ep + 1);
+                brick_restrict<T, D, VEL>(C, buf, c0, gs, wa, W, last, tail_mx, ep + 1);
                 __syncthreads();
             }
             if (coarse && !last) {
@@ -1038,25 +1046,24 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_bricks(const LevTab<T> *__res
                 __syncthreads();
             }
             if (!last) continue;
-            if (coarse) {
+            const Tail &tail = plan->tail;
+            const int n = cload(&tail.n);
+            if (coarse && brick_has_rows(wg, n)) {
                 // the tail: rows dealt out to the workgroups of its level
                 const BrickLev *cb = &plan->lev[l + 1];
-                u64 *const mx = cload(&cb->mx), *const mb = cload(&cb->mb);
-                const unsigned ms = (unsigned)cload(&tab[l + 1].g.nel) * MW<T>;
-                const Tail &tail = plan->tail;
-                const int n = cload(&tail.n);
+                u64 *const mb = cload(&cb->mb);
                 const int *const comp = cload(&tail.comp);
                 const long long *const idx = cload(&tail.idx);
                 for (int t = threadIdx.x; t < tail_ld(n, sizeof(T)); t += BRICK_THREADS) {
                     T val[1] = {T(0)};
                     if (t < n) {
                         const unsigned at_[1] = {comp[t] * ms + (unsigned)idx[t] * MW<T>};
-                        collect<T, 1>(mx, at_, 1u, ep + 1, val, dead);
+                        collect<T, 1>(tail_mx, at_, 1u, ep + 1, val, dead);
                     }
                     bv[t] = val[0];
                 }
                 __syncthreads();
-                const int nact = cload(&cb->sy) * cload(&cb->sz), per = BRICK_THREADS / TAIL_LANES;
+                const int nact = cload(&cb->sy) * cload(&cb->sz), per = BRICK_TAIL_ROWS;
                 const T *Tm = static_cast<const T *>(cload(&tail.Tm));
                 for (int r0 = wg * per; r0 < n; r0 += nact * per) {
                     const int r = r0 + threadIdx.x / TAIL_LANES, u = threadIdx.x % TAIL_LANES;

@@ -335,6 +335,7 @@ struct LdsPlan {
 // component, in the order comp, z, y, x).  n == 0: no tail, the cycle
 // recurses to the coarsest level.
 constexpr int TAIL_MAX = 512;
+constexpr int TAIL_LANES = 8;   // lanes that share a row (tail_row)
 struct Tail {
     const void *Tm;
     const long long *idx;

@@ -777,8 +777,6 @@ __device__ inline long long tail_at(int n, int r, int j)
 // partial sums are added pairwise, so the order is the same in every kernel
 // that uses it.  Columns past n (up to whole blocks) are zero in Tm, and bv
 // holds zeros there.  Every lane of the wave must call it.
-constexpr int TAIL_LANES = 8;
-
 template <typename T>
 __device__ inline T tail_row(const T *__restrict__ Tm, int n, int r, int u, const T *bv)
 {
