@@ -17,7 +17,8 @@ constexpr int BRICK_MAX_WG = 256;
 // tail's matrix: BRICK_TAIL_ROWS at a time, dealt out in turn to those with a
 // box on that level.  The others do not read it.  Its mailbox has two copies,
 // used in turn by the cycles of a launch.
-constexpr int BRICK_TAIL_ROWS = BRICK_THREADS / TAIL_LANES, BRICK_TAIL_COPIES = 2;
+constexpr int BRICK_TAIL_ROWS = BRICK_THREADS / TAIL_LANES;
+constexpr int BRICK_TAIL_COPIES = 2;
 __host__ __device__ constexpr bool brick_has_rows(int wg, int n) { return wg * BRICK_TAIL_ROWS < n; }
 
 // What a pass over one component of a level (velocity component, or the

@@ -705,10 +705,10 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_brick_tables(const LevTab<T> 
 // Second step of the restriction: components [c0, c0 + nc) of the coarse
 // right-hand side at the own points of the coarse brick C, from the x sums of
 // the lines around them in `buf`: into C's global b, or (last: C is the
-// tail's level) into tail_mx, the cycle's copy of its mx.
+// tail's level) into its mx, `copy` words on.
 template <typename T, int D, int VEL>
 BRICK_FN void brick_restrict(const Brick<T, D, VEL> &C, const double *buf, int c0, int nc, const WindowAt &wa, int W,
-                             bool last, u64 *tail_mx, unsigned ep)
+                             bool last, unsigned copy, unsigned ep)
 {
     each_own<T, D, VEL>(C, c0, nc, [&](int a, int s, int, int J, int K, int I) {
         // three lines per axis of faces, four per axis of cells (the fourth
@@ -743,7 +743,7 @@ BRICK_FN void brick_restrict(const Brick<T, D, VEL> &C, const double *buf, int c
         }
         const int e = (int)at(C.g, I, J, K);
         const BrickPass *P = &C.b->pass[a];
-        if (last) post<T>(tail_mx + (P->mail + (unsigned)e * MW<T>), (T)sum, ep);
+        if (last) post<T>(C.mx0 + (P->mail + copy + (unsigned)e * MW<T>), (T)sum, ep);
         else C.arr((unsigned)e * (unsigned)sizeof(T) + P->coef[0]) = (T)sum;
     });
 }
@@ -907,6 +907,7 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_bricks(const LevTab<T> *__res
     } else {
         const int nl = lc - lm + 1;
         Pending carry{PEND_NONE, 0, 0, 0};
+        unsigned copy = 0;   // words to the cycle's copy of the tail level's mx
 #pragma unroll 1
         for (int v = 0; v < 2 * nl * ncyc; ++v) {
             const int vv = v % (2 * nl);
@@ -999,9 +1000,6 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_bricks(const LevTab<T> *__res
             ++ep;
             const bool coarse = has_box(&plan->lev[l + 1], wg);
             const int gs = cload(&plan->lev[l].gs);
-            // the tail level's right-hand side, in the cycle's copy
-            const unsigned ms = (unsigned)cload(&tab[l + 1].g.nel) * MW<T>;
-            u64 *const tail_mx = cload(&plan->lev[l + 1].mx) + (unsigned)(v / (2 * nl) % BRICK_TAIL_COPIES) * (NC * ms);
             if (act) {
                 fetch<T, D, VEL>(B, S, pd, dead);
                 __syncthreads();
@@ -1035,7 +1033,7 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_bricks(const LevTab<T> *__res
                 fetch_window<double>(cload(&C.b->from_s) + (size_t)wg * cload(&C.b->ns) + c0 * one, gs * one, B.mb0, ep,
                                      buf, dead);
                 __syncthreads();
-                brick_restrict<T, D, VEL>(C, buf, c0, gs, wa, W, last, tail_mx, ep + 1);
+                brick_restrict<T, D, VEL>(C, buf, c0, gs, wa, W, last, copy, ep + 1);
                 __syncthreads();
             }
             if (coarse && !last) {
@@ -1048,17 +1046,18 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_bricks(const LevTab<T> *__res
             if (!last) continue;
             const Tail &tail = plan->tail;
             const int n = cload(&tail.n);
+            const unsigned ms = (unsigned)cload(&tab[l + 1].g.nel) * MW<T>;
             if (coarse && brick_has_rows(wg, n)) {
                 // the tail: rows dealt out to the workgroups of its level
                 const BrickLev *cb = &plan->lev[l + 1];
-                u64 *const mb = cload(&cb->mb);
+                u64 *const mx = cload(&cb->mx), *const mb = cload(&cb->mb);
                 const int *const comp = cload(&tail.comp);
                 const long long *const idx = cload(&tail.idx);
                 for (int t = threadIdx.x; t < tail_ld(n, sizeof(T)); t += BRICK_THREADS) {
                     T val[1] = {T(0)};
                     if (t < n) {
-                        const unsigned at_[1] = {comp[t] * ms + (unsigned)idx[t] * MW<T>};
-                        collect<T, 1>(tail_mx, at_, 1u, ep + 1, val, dead);
+                        const unsigned at_[1] = {copy + comp[t] * ms + (unsigned)idx[t] * MW<T>};
+                        collect<T, 1>(mx, at_, 1u, ep + 1, val, dead);
                     }
                     bv[t] = val[0];
                 }
@@ -1071,6 +1070,7 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_bricks(const LevTab<T> *__res
                     if (r < n && u == 0) post<T>(mb + (comp[r] * ms + (unsigned)idx[r] * MW<T>), sum, ep + 2);
                 }
             }
+            copy = copy ? 0u : NC * ms;
             ep += 2;
         }
     }
