@@ -61,7 +61,7 @@ typedef enum {
     IBB_EINVAL = 1,   /* bad descriptor, shape, size or pointer */
     IBB_ENOMEM = 2,   /* workspace smaller than ibb_footprint_bytes */
     IBB_ENOCONV = 3,  /* a solve hit max_cycles before reaching rtol */
-    IBB_ENUMERIC = 4, /* NaN or Inf in a residual norm */
+    IBB_ENUMERIC = 4, /* NaN or Inf in a residual norm, or a value lost between workgroups of a V-cycle */
     IBB_EDEVICE = 5,  /* a HIP runtime call failed */
     IBB_ESTATE = 6    /* call out of order (e.g. a step before coefficients) */
 } ibb_status;

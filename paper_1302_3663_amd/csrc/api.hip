@@ -119,6 +119,7 @@ struct ibb_ctx {
     // launch pass by pass although there are bricks (see pass_by_pass), and
     // for good once a launch of bricks did not find its workgroups together
     bool plain = false, apart = false;
+    int lost = 0;     // BrickCtl::lost as last seen
     int dev = 0;
     // nodes and springs
     long long eta_max = 0, m_max = 0;
@@ -1257,7 +1258,8 @@ void vcycles_from_zero(ibb_ctx *c, bool vel, int n)
 }
 
 // the reduced scalar back on the host; a launch of bricks that had to run on
-// one workgroup is the last (the device is shared with another process)
+// one workgroup is the last (the device is shared with another process), and
+// so is one that lost a value, whose result is worthless
 ibb_status fetch_scalar(ibb_ctx *c, double *out)
 {
     struct {
@@ -1268,6 +1270,11 @@ ibb_status fetch_scalar(ibb_ctx *c, double *out)
     HIPCHK(hipStreamSynchronize(c->s));
     *out = h.scalar;
     if (h.ctl.solo_runs && h.ctl.limit) c->apart = true;
+    if (h.ctl.lost != c->lost) {
+        c->lost = h.ctl.lost;
+        c->apart = true;
+        return fail(c, IBB_ENUMERIC, "a V-cycle lost a value between its workgroups");
+    }
     return IBB_OK;
 }
 
@@ -2313,6 +2320,13 @@ int ibmg_bricks_control(ibb_ctx *c, int on, long long limit, int first_level[2],
     if (solo_runs) *solo_runs = ctl.lost ? -ctl.lost : ctl.solo_runs;
     ctl.limit = limit < 0 ? BRICK_WAIT : limit;
     return hipMemcpy(c->bctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice) == hipSuccess ? 0 : 1;
+}
+
+// Not part of the interface (tests): as if n workgroups had given up.
+int ibmg_bricks_lose(ibb_ctx *c, int n)
+{
+    if (!c->bctl || hipStreamSynchronize(c->s) != hipSuccess) return 1;
+    return hipMemcpy(&c->bctl->lost, &n, sizeof(n), hipMemcpyHostToDevice) == hipSuccess ? 0 : 1;
 }
 
 ibb_status ibb_destroy(ibb_ctx *c)

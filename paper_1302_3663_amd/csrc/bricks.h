@@ -88,7 +88,7 @@ struct BrickCtl {
     unsigned arrive, state, done, epoch;
     long long limit;
     int solo_runs;    // launches that ran on one workgroup
-    int lost;         // workgroups that gave up waiting for a value
+    int lost;         // workgroups that gave up waiting for a value: such results are worthless
 };
 
 __host__ __device__ constexpr int brick_mail_words(int wsz) { return wsz / 4; }

@@ -53,7 +53,9 @@ namespace ibmg {
 
 typedef unsigned long long u64;
 // polls before a workgroup gives up on a value (seconds; only a lost
-// neighbour could cause it) and returns NaN
+// neighbour could cause it).  From then on NaN takes the place of what it hands
+// on from level to level and of its result, and it counts itself in
+// BrickCtl::lost, which the host turns into an error.
 constexpr int BRICK_POLLS = 1 << 21;
 
 template <typename T>
@@ -106,6 +108,9 @@ BRICK_FN void collect(const u64 *box, const unsigned (&w)[N], unsigned need, uns
         else v[u] = (T)__longlong_as_double((long long)((x[u][0] & 0xffffffffull) | (x[u][MW<T> - 1] << 32)));
     }
 }
+
+// whether this workgroup has given up on a value
+BRICK_FN bool gave_up(const int *dead) { return *(const volatile int *)dead != 0; }
 
 // words of a read-only table through scalar loads (every lane reads the same)
 template <typename S>
@@ -708,8 +713,9 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_brick_tables(const LevTab<T> 
 // tail's level) into its mx, `copy` words on.
 template <typename T, int D, int VEL>
 BRICK_FN void brick_restrict(const Brick<T, D, VEL> &C, const double *buf, int c0, int nc, const WindowAt &wa, int W,
-                             bool last, unsigned copy, unsigned ep)
+                             bool last, unsigned copy, unsigned ep, const int *dead)
 {
+    const bool lost = gave_up(dead);
     each_own<T, D, VEL>(C, c0, nc, [&](int a, int s, int, int J, int K, int I) {
         // three lines per axis of faces, four per axis of cells (the fourth
         // weight of faces is zero and its line read again)
@@ -741,6 +747,7 @@ BRICK_FN void brick_restrict(const Brick<T, D, VEL> &C, const double *buf, int c
                 sum += w1[b] * w2[c] * v[b];
             }
         }
+        if (lost) sum = __builtin_nan("");
         const int e = (int)at(C.g, I, J, K);
         const BrickPass *P = &C.b->pass[a];
         if (last) post<T>(C.mx0 + (P->mail + copy + (unsigned)e * MW<T>), (T)sum, ep);
@@ -821,7 +828,7 @@ BRICK_FN void brick_prolong(const Brick<T, D, VEL> &B, const Slot *own, const T 
 template <typename T, int D, int VEL>
 BRICK_FN void brick_out(const Brick<T, D, VEL> &B, bool final, unsigned ep, const int *dead)
 {
-    const bool lost = final && *(const volatile int *)dead;
+    const bool lost = gave_up(dead);
     each_own<T, D, VEL>(B, 0, B.NC, [&](int a, int, int, int j, int k, int i) {
         const BrickPass *P = &B.b->pass[a];
         const T v = lost ? (T)__builtin_nan("") : B.win((B.line_entry(j, k) + i) * (int)sizeof(T) + P->win[0]);
@@ -1033,7 +1040,7 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_bricks(const LevTab<T> *__res
                 fetch_window<double>(cload(&C.b->from_s) + (size_t)wg * cload(&C.b->ns) + c0 * one, gs * one, B.mb0, ep,
                                      buf, dead);
                 __syncthreads();
-                brick_restrict<T, D, VEL>(C, buf, c0, gs, wa, W, last, copy, ep + 1);
+                brick_restrict<T, D, VEL>(C, buf, c0, gs, wa, W, last, copy, ep + 1, dead);
                 __syncthreads();
             }
             if (coarse && !last) {
@@ -1058,6 +1065,7 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_bricks(const LevTab<T> *__res
                     if (t < n) {
                         const unsigned at_[1] = {copy + comp[t] * ms + (unsigned)idx[t] * MW<T>};
                         collect<T, 1>(mx, at_, 1u, ep + 1, val, dead);
+                        if (gave_up(dead)) val[0] = (T)__builtin_nan("");   // a term of every row
                     }
                     bv[t] = val[0];
                 }
