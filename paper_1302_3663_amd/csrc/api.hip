@@ -536,9 +536,6 @@ long long tail_lds_bytes(const ibb_ctx *c, bool f32, bool vel, int lt)
     return b;
 }
 
-// LDS of a brick workgroup: the CU's, less the kernel's own shared data;
-// fixed, as TAIL_LDS_BUDGET
-constexpr int BRICK_LDS_BUDGET = 163840 - (int)(TAIL_MAX * sizeof(double)) - 256;
 // a workgroup that has waited this long for the others to start (100 MHz
 // ticks: 20 ms) runs the cycle by itself
 constexpr long long BRICK_WAIT = 2000000;

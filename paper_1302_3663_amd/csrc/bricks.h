@@ -13,6 +13,8 @@ constexpr int BRICK_THREADS = 512;
 constexpr int BRICK_SLOTS = 3;
 // workgroups at most (one per CU of the chip)
 constexpr int BRICK_MAX_WG = 256;
+// LDS of a workgroup at most: the CU's, less the kernel's own shared data
+constexpr int BRICK_LDS_BUDGET = 163840 - (int)(TAIL_MAX * sizeof(double)) - 256;
 // The tail level's right-hand side goes to every workgroup with rows of the
 // tail's matrix: BRICK_TAIL_ROWS at a time, dealt out in turn to those with a
 // box on that level.  The others do not read it.  Its mailbox has two copies,

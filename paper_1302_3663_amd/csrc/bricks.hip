@@ -1096,17 +1096,14 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_bricks(const LevTab<T> *__res
 }
 
 template <typename T, int D, int VEL>
-static bool allow_bricks(int bytes)
-{
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(k_bricks<T, D, VEL>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
-}
-
-template <typename T, int D, int VEL>
 static int resident(int bytes)
 {
     int dev = 0, cus = 0, per = 0;
-    if (!allow_bricks<T, D, VEL>(bytes) || hipGetDevice(&dev) != hipSuccess ||
+    // the limit is the kernel's, for every context of the process: always the
+    // whole budget, never this plan's bytes, which may be fewer than another's
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(k_bricks<T, D, VEL>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, BRICK_LDS_BUDGET) != hipSuccess ||
+        hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_bricks<T, D, VEL>, BRICK_THREADS, bytes) != hipSuccess) {
         (void)hipGetLastError();   // the levels are launched pass by pass instead
