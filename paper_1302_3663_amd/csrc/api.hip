@@ -2980,13 +2980,19 @@ void plan_tick(Plan &P, std::vector<GOp> &ops, const std::vector<ibb_ctx *> &m, 
     } else {
         plan_vcycle(P, ops, m, 0, vel, nu1, nu2);
     }
-    plan_pass(P, ops, m, all, BK_RESID, 0, vel, 0, 0, 0, true);
+    for (int kind : {BK_RESID, BK_RESID_ROWS}) {
+        std::vector<int> w;
+        for (int i : all)
+            if (norm_pass(m[i]->lv[0].g, vel ? 1 : 0) == kind) w.push_back(i);
+        plan_pass(P, ops, m, w, kind, 0, vel, 0, 0, 0, true);
+    }
     GOp red{GK_REDUCE, 0, 0, vel ? 1 : 0, 0, 0, P.ent.size(), 0, 0};
     for (size_t i = 0; i < m.size(); ++i) {
         ibb_ctx *c = m[i];
         BEntry e{};
         e.partial = c->partial;
-        e.nb = batch_blocks(BK_RESID, c->lv[0].g, c->lv[0].g, vel ? 1 : 0, 0) * (vel ? c->d.dim : 1);
+        const Grid &g0 = c->lv[0].g;
+        e.nb = batch_blocks(norm_pass(g0, vel ? 1 : 0), g0, g0, vel ? 1 : 0, 0) * (vel ? c->d.dim : 1);
         e.ctx = (int)i;
         P.ent.push_back(e);
         red.n++;

@@ -70,8 +70,8 @@ __host__ __device__ inline bool box_colour_pos(const Box &b, int colour, int t, 
 constexpr int ROW_MIN = 24;
 constexpr int ROW_WAVES = 4;   // of a workgroup
 
-inline bool rows_by_waves(const Box &b) { return b.ext[0] >= ROW_MIN; }
-inline unsigned row_blocks(const Box &b)
+__host__ __device__ inline bool rows_by_waves(const Box &b) { return b.ext[0] >= ROW_MIN; }
+__host__ __device__ inline unsigned row_blocks(const Box &b)
 {
     const long long waves = (long long)((b.ext[0] + 63) / 64) * b.ext[1] * b.ext[2];
     return (unsigned)((waves + ROW_WAVES - 1) / ROW_WAVES);
@@ -513,7 +513,9 @@ struct BCoarse {
 };
 
 // pass kinds
-enum { BK_SWEEP = 0, BK_RESID = 1, BK_RESTRICT = 2, BK_PROLONG = 3, BK_PREP = 4, BK_ADD = 5 };
+enum { BK_SWEEP = 0, BK_RESID = 1, BK_RESTRICT = 2, BK_PROLONG = 3, BK_PREP = 4, BK_ADD = 5, BK_RESID_ROWS = 6 };
+// the kind that adds up a residual's norm in the order of a solve alone
+int norm_pass(const Grid &g, int vel);
 // blocks one context needs in a batched pass of kind `kind` on level grid g
 // (gc: the next coarser grid, for restriction); A: component of a sweep
 int batch_blocks(int kind, const Grid &g, const Grid &gc, int vel, int A);

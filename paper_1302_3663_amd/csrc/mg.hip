@@ -38,10 +38,9 @@ constexpr long long XCD_REMAP_MAX_NEL = 16ll << 20;
 // order on arrays of 4.4 M entries and 5-7% slower on 34.5 M, where the planes
 // a point reads no longer fit an XCD's L2; strips are 1-2% faster there.
 // ---------------------------------------------------------------------------
-__device__ inline unsigned xcd_block(int remap)
+__device__ inline unsigned xcd_block(int remap, unsigned b, unsigned nb)
 {
     constexpr unsigned NXCD = 8;
-    const unsigned nb = gridDim.x, b = blockIdx.x;
     if (!remap) return b;
     if (remap > 0) {
         const unsigned n = (unsigned)remap, round = NXCD * n, r = b / round, t = b - r * round;
@@ -51,10 +50,12 @@ __device__ inline unsigned xcd_block(int remap)
     return x * q + (x < r ? x : r) + b / NXCD;
 }
 
-static int xcd_remap(const Grid &g, const Box &box, long long blocks)
+__device__ inline unsigned xcd_block(int remap) { return xcd_block(remap, blockIdx.x, gridDim.x); }
+
+__host__ __device__ static inline int xcd_remap(const Grid &g, const Box &box, long long blocks)
 {
-    const long long planes = g.D == 3 ? box.ext[2] : box.ext[1];
-    return g.nel <= XCD_REMAP_MAX_NEL ? -1 : (int)std::max<long long>(1, (blocks / planes + 4) / 8);
+    const long long planes = g.D == 3 ? box.ext[2] : box.ext[1], n = (blocks / planes + 4) / 8;
+    return g.nel <= XCD_REMAP_MAX_NEL ? -1 : (int)(n > 1 ? n : 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -629,11 +630,71 @@ __global__ void __launch_bounds__(256) k_resid_u(Grid g, VelBox boxes, VelArrC<T
     if (partial) block_sum_store(acc, partial, (long long)blockIdx.y * gridDim.x + blockIdx.x);
 }
 
+// From so many points a component on, the waves of one round of components
+// fill the chip several times over; below, each component has its own.
+constexpr long long RESID_ALL_MIN = 1ll << 20;
+
+// How the rows of a level's velocity residual are dealt out: `all` holds the
+// rows of every component, in `blocks` blocks of waves; with norms nb blocks
+// take them in rounds, and a block's place in the partial sums is its number
+// before the remapping.  The same for a solve alone and in a group, so that
+// both add up a norm in the same order.
+struct ResidRows {
+    Box all;
+    unsigned blocks, nb;
+    int remap;
+    bool large, norm;   // all components in turn; rows by waves with norms too
+};
+__host__ __device__ static inline ResidRows resid_rows(const Grid &g)
+{
+    ResidRows R;
+    R.all = unk_box(g, face_mask(0));
+    const bool rows = rows_by_waves(R.all);
+    long long mx = 0;
+    for (int a = 0; a < g.D; ++a) {
+        const Box b = unk_box(g, face_mask(a));
+        const long long n = (long long)b.ext[0] * b.ext[1] * b.ext[2];
+        mx = n > mx ? n : mx;
+        for (int d = 0; d < 3; ++d) {
+            const int he = R.all.lo[d] + R.all.ext[d], hb = b.lo[d] + b.ext[d];
+            R.all.lo[d] = b.lo[d] < R.all.lo[d] ? b.lo[d] : R.all.lo[d];
+            R.all.ext[d] = (hb > he ? hb : he) - R.all.lo[d];
+        }
+    }
+    R.large = mx >= RESID_ALL_MIN;
+    R.norm = rows && R.large;
+    R.blocks = row_blocks(R.all);
+    R.nb = R.blocks < NORM_BLOCKS_MAX ? R.blocks : NORM_BLOCKS_MAX;
+    R.remap = xcd_remap(g, R.all, R.blocks);
+    return R;
+}
+
+// Components [a0, a1) of the residual at the points of block blk of the rows;
+// NORM: their squares added to acc
+template <typename T, int D, bool NORM>
+__device__ inline void resid_u_block(const Grid &g, const Box &all, const VelBox &boxes, const VelArrC<T> &b,
+                                     const VelArr<T> &x, const CoefU<T> &cf, T mass, T cvisc, const VelArr<T> &r, int a0,
+                                     int a1, unsigned blk, double acc[3])
+{
+    constexpr int A2 = D == 3 ? 2 : 1;
+    int i, j, k;
+    if (!row_pos(all, blk, i, j, k)) return;
+    auto in = [&](const Box &q) {
+        return i >= q.lo[0] && i < q.lo[0] + q.ext[0] && j >= q.lo[1] && j < q.lo[1] + q.ext[1] && k >= q.lo[2] &&
+               k < q.lo[2] + q.ext[2];
+    };
+    auto add = [&](int a, T v) {
+        if (NORM) acc[a] += (double)v * (double)v;
+    };
+    if (a0 == 0 && in(boxes.b[0])) add(0, resid_u_at<T, D, 0>(g, b, x, cf, mass, cvisc, r, i, j, k));
+    if (a0 <= 1 && a1 > 1 && in(boxes.b[1])) add(1, resid_u_at<T, D, 1>(g, b, x, cf, mass, cvisc, r, i, j, k));
+    if (D == 3 && a1 > 2 && in(boxes.b[2])) add(2, resid_u_at<T, D, A2>(g, b, x, cf, mass, cvisc, r, i, j, k));
+}
+
 // The residual, rows by waves: `ncomp` components from blockIdx.y on, in turn,
 // so that what they share (the velocities, the viscosities) comes from the
-// caches.  `all` holds the rows of all of them.  NORM: all components and
-// their squared norms, rounds of gridDim.x blocks, partial sums per component
-// and block.  Numbered through in a grid-stride loop over one component
+// caches.  NORM: all components and their squared norms, rounds of gridDim.x
+// blocks, partial sums per component and block.  Numbered through in a grid-stride loop over one component
 // (k_resid_u), the divisions of the index and each component's own fetch of
 // what they share bound it: 1110 us at 256 x 256 x 512 in FP32 against 725, in
 // FP64 with norms 2080 against 1580; 98 against 61 at 128 x 128 x 256 in FP32.
@@ -642,23 +703,10 @@ __global__ void __launch_bounds__(256) k_resid_u_rows(Grid g, Box all, VelBox bo
                                                       CoefU<T> cf, T mass, T cvisc, VelArr<T> r, int ncomp, int remap,
                                                       unsigned blocks, double *partial)
 {
-    constexpr int A2 = D == 3 ? 2 : 1;
     const int a0 = NORM ? 0 : blockIdx.y, a1 = NORM ? D : a0 + ncomp;
     double acc[3] = {0.0, 0.0, 0.0};
     for (unsigned blk = xcd_block(remap); blk < blocks; blk += gridDim.x) {
-        int i, j, k;
-        if (row_pos(all, blk, i, j, k)) {
-            auto in = [&](const Box &q) {
-                return i >= q.lo[0] && i < q.lo[0] + q.ext[0] && j >= q.lo[1] && j < q.lo[1] + q.ext[1] &&
-                       k >= q.lo[2] && k < q.lo[2] + q.ext[2];
-            };
-            auto add = [&](int a, T v) {
-                if (NORM) acc[a] += (double)v * (double)v;
-            };
-            if (a0 == 0 && in(boxes.b[0])) add(0, resid_u_at<T, D, 0>(g, b, x, cf, mass, cvisc, r, i, j, k));
-            if (a0 <= 1 && a1 > 1 && in(boxes.b[1])) add(1, resid_u_at<T, D, 1>(g, b, x, cf, mass, cvisc, r, i, j, k));
-            if (D == 3 && a1 > 2 && in(boxes.b[2])) add(2, resid_u_at<T, D, A2>(g, b, x, cf, mass, cvisc, r, i, j, k));
-        }
+        resid_u_block<T, D, NORM>(g, all, boxes, b, x, cf, mass, cvisc, r, a0, a1, blk, acc);
         if (!NORM) return;
     }
 #pragma unroll
@@ -1341,6 +1389,31 @@ __global__ void __launch_bounds__(256) k_bresid(const BEntry *__restrict__ ent, 
     if (E.partial) block_sum_store(acc, E.partial, (long long)a * E.nb + lb);
 }
 
+// the velocity residual of large members with its norm, rows by waves: the
+// blocks, rounds and sums of k_resid_u_rows
+template <typename T, int D>
+__global__ void __launch_bounds__(256) k_bresid_rows(const BEntry *__restrict__ ent, const int *__restrict__ flags)
+{
+    const BEntry E = ent[blockIdx.x];
+    const int on = flags[E.ctx];
+    const LevTab<T> lt = tab_copy<T>(E.tab);
+    if (!on) return;
+    const unsigned lb = blockIdx.x - E.base;
+    const ResidRows R = resid_rows(lt.g);
+    VelBox boxes;
+    for (int a = 0; a < D; ++a) boxes.b[a] = unk_box(lt.g, face_mask(a));
+    const VelArr<T> x{{lt.xu[0], lt.xu[1], lt.xu[2]}}, r{{lt.ru[0], lt.ru[1], lt.ru[2]}};
+    const VelArrC<T> b{{lt.bu[0], lt.bu[1], lt.bu[2]}};
+    double acc[3] = {0.0, 0.0, 0.0};
+    for (unsigned blk = xcd_block(R.remap, lb, R.nb); blk < R.blocks; blk += R.nb)
+        resid_u_block<T, D, true>(lt.g, R.all, boxes, b, x, coef_u(lt), lt.mass, lt.cvu, r, 0, D, blk, acc);
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        block_sum_store(acc[a], E.partial, (long long)a * R.nb + lb);
+        __syncthreads();
+    }
+}
+
 // one block per context: norms[ctx] = sum of its E.nb partial sums, in the
 // order of the single-context final reduction
 __global__ void __launch_bounds__(256) k_breduce(const BEntry *__restrict__ ent, const int *__restrict__ flags,
@@ -1636,12 +1709,6 @@ int launch_resid_p(const Grid &g, const T *b, const T *x, const CoefP<T> &cf, T 
     return (int)nb;
 }
 
-// From so many points a component on, the waves of one round of components
-// fill the chip several times over; below, each component has its own.  With
-// norms, rows by waves only from there on: below, the order of the sums is
-// that of the solves in groups.
-constexpr long long RESID_ALL_MIN = 1ll << 20;
-
 template <typename T>
 int launch_resid_u(const Grid &g, const VelArrC<T> &b, const VelArr<T> &x, const CoefU<T> &cf, T mass, T cvisc,
                    const VelArr<T> &r, double *partial, hipStream_t s)
@@ -1652,20 +1719,14 @@ int launch_resid_u(const Grid &g, const VelArrC<T> &b, const VelArr<T> &x, const
         parts.b[a] = a < g.D ? unk_box(g, face_mask(a)) : Box{{0, 0, 0}, {0, 0, 0}};
         if (a < g.D && box_count(parts.b[a]) > mx) mx = box_count(parts.b[a]);
     }
-    const bool large = mx >= RESID_ALL_MIN;
-    if (rows_by_waves(parts.b[0]) && (large || !partial)) {
-        Box all = parts.b[0];
-        for (int a = 1; a < g.D; ++a)
-            for (int d = 0; d < 3; ++d) {
-                const int hi = std::max(all.lo[d] + all.ext[d], parts.b[a].lo[d] + parts.b[a].ext[d]);
-                all.lo[d] = std::min(all.lo[d], parts.b[a].lo[d]);
-                all.ext[d] = hi - all.lo[d];
-            }
-        const unsigned blocks = row_blocks(all), nb = partial ? std::min(blocks, NORM_BLOCKS_MAX) : blocks;
-        const dim3 grid(nb, large ? 1 : g.D), blk(256);
-        const int nc = large ? g.D : 1, remap = xcd_remap(g, all, blocks);
-#define LAUNCH(DD, NN) \
-    launch_timed(k_resid_u_rows<T, DD, NN>, grid, blk, s, g, all, parts, b, x, cf, mass, cvisc, r, nc, remap, blocks, partial)
+    const ResidRows R = resid_rows(g);
+    if (rows_by_waves(parts.b[0]) && (R.large || !partial)) {
+        const unsigned nb = partial ? R.nb : R.blocks;
+        const dim3 grid(nb, R.large ? 1 : g.D), blk(256);
+        const int nc = R.large ? g.D : 1;
+#define LAUNCH(DD, NN)                                                                                             \
+    launch_timed(k_resid_u_rows<T, DD, NN>, grid, blk, s, g, R.all, parts, b, x, cf, mass, cvisc, r, nc, R.remap, \
+                 R.blocks, partial)
         if (g.D == 3) {
             if (partial) LAUNCH(3, true);
             else LAUNCH(3, false);
@@ -1983,6 +2044,8 @@ template void launch_tail_columns<double>(int, const LevTab<double> *, int, int,
 template void launch_tail_columns<float>(int, const LevTab<float> *, int, int, int, int, int, const long long *,
                                          const int *, const double *, const LdsPlan &, const Tail &, hipStream_t);
 
+int norm_pass(const Grid &g, int vel) { return vel && resid_rows(g).norm ? BK_RESID_ROWS : BK_RESID; }
+
 int batch_blocks(int kind, const Grid &g, const Grid &gc, int vel, int A)
 {
     const int nc = vel ? g.D : 1;
@@ -1995,6 +2058,7 @@ int batch_blocks(int kind, const Grid &g, const Grid &gc, int vel, int A)
     case BK_RESID:
         for (int a = 0; a < nc; ++a) mx = std::max(mx, box_count(unk_box(g, vel ? face_mask(a) : 0)));
         return (int)stride_blocks(mx);
+    case BK_RESID_ROWS: return (int)resid_rows(g).nb;
     case BK_RESTRICT:
         for (int a = 0; a < nc; ++a) mx = std::max(mx, box_count(unk_box(gc, vel ? face_mask(a) : 0)));
         return (int)blocks_for(mx);
@@ -2042,6 +2106,10 @@ void launch_bpass(int kind, int D, int vel, int A, int colour, const BEntry *ent
     case BK_RESID:
         if (D == 3) PASS3(k_bresid);
         else PASS2(k_bresid);
+        break;
+    case BK_RESID_ROWS:
+        if (D == 3) hipLaunchKernelGGL((k_bresid_rows<T, 3>), dim3(nblocks), blk, 0, s, ent, flags);
+        else hipLaunchKernelGGL((k_bresid_rows<T, 2>), dim3(nblocks), blk, 0, s, ent, flags);
         break;
     case BK_RESTRICT:
         if (D == 3) PASS3(k_brestrict);
