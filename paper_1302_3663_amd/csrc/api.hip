@@ -1766,10 +1766,10 @@ void coarsest_tables(ibb_ctx *c, std::vector<long long> &ip, std::vector<int> &c
 // Room for the table of a spread: the finest level's pressure right-hand side
 // and residual, which hold nothing between solves (carved one after the
 // other).
-NodeTab solver_node_table(ibb_ctx *c, double width, int eta)
+NodeTab solver_node_table(ibb_ctx *c, const Bins &bins, double width, int eta)
 {
     const Level &L0 = c->lv[0];
-    return node_table(L0.g, width, eta, L0.bp, (L0.rp - L0.bp) + L0.g.nel);
+    return node_table(L0.g, bins, width, eta, L0.bp, (L0.rp - L0.bp) + L0.g.nel);
 }
 
 // spread, coarse coefficients, FP32 copies, coarsest inverses
@@ -1791,7 +1791,7 @@ ibb_status rebuild_coefficients(ibb_ctx *c)
     bins_for_width(d, d->omega, b.nb, b.bs);
     b.nbins = b.nb[0] * b.nb[1] * b.nb[2];
     launch_bin_nodes(L0.g, b, c->X, em, c->eta, c->scan_tmp, c->s);
-    const NodeTab tab = solver_node_table(c, d->omega, c->eta);
+    const NodeTab tab = solver_node_table(c, b, d->omega, c->eta);
     launch_node_table(L0.g, d->kernel, b, c->X, c->F, em, c->eta, d->omega, tab, c->s);
     for (int a = 0; a < D; ++a) {
         Timed t(c, PS_SPREAD_FACE, 0, lattice_count(L0.g, face_mask(a)));
@@ -2653,7 +2653,7 @@ ibb_status ibb_spread(ibb_ctx *c, double width, int64_t n, const double *X, cons
     bins_for_width(&c->d, width, b.nb, b.bs);
     b.nbins = b.nb[0] * b.nb[1] * b.nb[2];
     launch_bin_nodes(L0.g, b, X, n > 0 ? n : 1, (int)n, c->scan_tmp, c->s);
-    const NodeTab tab = solver_node_table(c, width, (int)n);
+    const NodeTab tab = solver_node_table(c, b, width, (int)n);
     launch_node_table(L0.g, c->d.kernel, b, X, F, n, (int)n, width, tab, c->s);
     for (int a = 0; a < c->d.dim; ++a)
         launch_spread_face(L0.g, c->ph, b, tab, X, F, n > 0 ? n : 1, a, width, L0.ru[a], nullptr, c->s);

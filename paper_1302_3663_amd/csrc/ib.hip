@@ -398,22 +398,6 @@ __global__ void __launch_bounds__(256) k_node_table(Grid g, int kernel, Bins bin
     }
 }
 
-NodeTab node_table(const Grid &g, double width, int eta, double *at, long long room)
-{
-    NodeTab t{nullptr, 0, 0};
-    long long points = 1;
-    for (int d = 0; d < g.D; ++d) points *= stored_extent(g, d, 1);
-    const double nt = ceil(4.0 * width / g.h) + 2.0;
-    if (eta <= 0 || points <= SPREAD_WAVE_MAX_POINTS || nt > 64.0) return t;
-    // an index of a short periodic axis could lie in a run twice
-    for (int d = 0; d < g.D; ++d)
-        if (g.bc[d] == AX_PERIODIC && nt > g.n[d]) return t;
-    t.nt = (int)nt;
-    t.record = 8 + 2 * g.D * t.nt;
-    if ((long long)eta * t.record <= room) t.rec = at;
-    return t;
-}
-
 // A wave takes a box of 8 x 4 x 2 lattice points (8 x 8 in two dimensions) and
 // walks the nodes of all bins that any of them looks at, in the order of
 // bin_candidates, so that ranges, indices and records are scalar and the lanes
@@ -571,6 +555,34 @@ struct BoxGather {
         }
     }
 };
+
+// Whether boxes of E points along periodic axis d may look at all its bins and
+// a point at some only.  Their walk would start at the axis' first bin and the
+// point's own before its wrap, and add up the nodes in another order.
+static bool walk_wraps(const Grid &g, const Bins &bins, int d, int E)
+{
+    return g.bc[d] == AX_PERIODIC && bins.nb[d] > 2 * BIN_REACH &&
+           (E - 1) * g.h / bins.bs[d] + 2.0 + 2 * BIN_REACH >= bins.nb[d];
+}
+
+NodeTab node_table(const Grid &g, const Bins &bins, double width, int eta, double *at, long long room)
+{
+    NodeTab t{nullptr, 0, 0};
+    long long points = 1;
+    for (int d = 0; d < g.D; ++d) points *= stored_extent(g, d, 1);
+    const double nt = ceil(4.0 * width / g.h) + 2.0;
+    if (eta <= 0 || points <= SPREAD_WAVE_MAX_POINTS || nt > 64.0) return t;
+    // an index of a short periodic axis could lie in a run twice
+    for (int d = 0; d < g.D; ++d)
+        if (g.bc[d] == AX_PERIODIC && nt > g.n[d]) return t;
+    const int E[3] = {BoxGather<3>::BX, g.D == 3 ? BoxGather<3>::BY : BoxGather<2>::BY, BoxGather<3>::BZ};
+    for (int d = 0; d < g.D; ++d)
+        if (walk_wraps(g, bins, d, E[d])) return t;
+    t.nt = (int)nt;
+    t.record = 8 + 2 * g.D * t.nt;
+    if ((long long)eta * t.record <= room) t.rec = at;
+    return t;
+}
 
 // this wave's box of a lattice: four along x to a workgroup
 template <int D>

@@ -575,9 +575,10 @@ struct NodeTab {
     double *rec;
     int nt, record;
 };
-// the table for a width, if lattices of the grid are spread point by point
-// and `room` doubles hold it
-NodeTab node_table(const Grid &g, double width, int eta, double *at, long long room);
+// the table for a width and its bins, if lattices of the grid are spread point
+// by point, the nodes are then added up in the same order and `room` doubles
+// hold it
+NodeTab node_table(const Grid &g, const Bins &bins, double width, int eta, double *at, long long room);
 void launch_node_table(const Grid &g, int kernel, const Bins &bins, const double *X, const double *F, long long stride,
                        int eta, double width, const NodeTab &tab, hipStream_t s);
 // tab: of these bins, nodes and F, or none
