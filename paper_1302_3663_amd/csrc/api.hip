@@ -116,9 +116,11 @@ struct ibb_ctx {
     BrickPlan *bplan_dev[2] = {};
     unsigned long long *bmx[MAXLEV] = {}, *bmb[MAXLEV] = {};
     BrickCtl *bctl = nullptr;     // behind the scalar, read back with it
-    // launch pass by pass although there are bricks (see pass_by_pass), and
-    // for good once a launch of bricks did not find its workgroups together
+    // launch pass by pass although there are bricks (see pass_by_pass): for
+    // good once a launch lost a value, and for a while after one that did not
+    // find its workgroups together (see BrickRest)
     bool plain = false, apart = false;
+    BrickRest brick_rest;
     int lost = 0;     // BrickCtl::lost as last seen
     int dev = 0;
     // nodes and springs
@@ -1254,9 +1256,9 @@ void vcycles_from_zero(ibb_ctx *c, bool vel, int n)
         for (int it = 0; it < n; ++it) vcycle<T>(c, vel, 0);
 }
 
-// the reduced scalar back on the host; a launch of bricks that had to run on
-// one workgroup is the last (the device is shared with another process), and
-// so is one that lost a value, whose result is worthless
+// the reduced scalar back on the host, and how the last launches of bricks
+// went: after one that had to run on one workgroup the context rests from
+// them; one that lost a value, whose result is worthless, is the last
 ibb_status fetch_scalar(ibb_ctx *c, double *out)
 {
     struct {
@@ -1266,7 +1268,7 @@ ibb_status fetch_scalar(ibb_ctx *c, double *out)
     HIPCHK(hipMemcpyAsync(&h, c->scalar, c->bctl ? sizeof(h) : sizeof(double), hipMemcpyDeviceToHost, c->s));
     HIPCHK(hipStreamSynchronize(c->s));
     *out = h.scalar;
-    if (h.ctl.solo_runs && h.ctl.limit) c->apart = true;
+    if (h.ctl.limit) c->brick_rest.saw(h.ctl.solo_runs);
     if (h.ctl.lost != c->lost) {
         c->lost = h.ctl.lost;
         c->apart = true;
@@ -1288,7 +1290,7 @@ struct Solving {
     explicit Solving(const ibb_ctx *c) : n(solving[c->dev & 63]) { n.fetch_add(1); }
     ~Solving() { n.fetch_sub(1); }
 };
-void pass_by_pass(ibb_ctx *c) { c->plain = c->apart || solving[c->dev & 63].load() > 1; }
+void pass_by_pass(ibb_ctx *c) { c->plain = c->apart || c->brick_rest.resting() || solving[c->dev & 63].load() > 1; }
 // index of the graphs of the present choice
 int graph_set(const ibb_ctx *c, bool vel) { return c->plain && c->bricks[vel ? 1 : 0] ? 1 : 0; }
 
@@ -1621,6 +1623,7 @@ ibb_status solve_gcr(ibb_ctx *c, bool vel, int max_cycles, int exact, SolveOut *
     R.exact = exact;
     R.o = o;
     Solving here(c);
+    c->brick_rest.solve_begins();
     ibb_status st = gcr_begin(R);
     if (st) return st;
     while (gcr_more(R)) {
@@ -1639,6 +1642,7 @@ ibb_status solve(ibb_ctx *c, bool vel, int max_cycles, int exact, SolveOut *o)
 {
     if (c->d.krylov_restart > 0) return solve_gcr(c, vel, max_cycles, exact, o);
     Solving here(c);
+    c->brick_rest.solve_begins();
     const bool refined = c->d.precision == IBB_FP32_REFINED;
     const int D = c->d.dim;
     int vm[3];

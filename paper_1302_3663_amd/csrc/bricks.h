@@ -93,6 +93,31 @@ struct BrickCtl {
     int lost;         // workgroups that gave up waiting for a value: such results are worthless
 };
 
+// When a context launches bricks again after a launch that ran on one
+// workgroup.  Something else held the chip then: a kernel of another stream,
+// once, or another process, all the time.  So the context rests for the
+// remainder of the solve and the next one; each further such launch doubles
+// the rest, up to BRICK_REST_MAX solves, and each solve between that ran
+// without one halves it.
+constexpr int BRICK_REST_MAX = 256;
+struct BrickRest {
+    int left = 0, next = 1;   // solves still to rest for, with the present one; length of the next rest
+    int seen = 0;             // launches on one workgroup so far
+    bool resting() const { return left > 0; }
+    void solve_begins()
+    {
+        if (left > 0) --left;
+        else if (next > 1) next /= 2;
+    }
+    void saw(int solo_runs)
+    {
+        if (solo_runs == seen) return;
+        seen = solo_runs;
+        left = next + 1;
+        next = next < BRICK_REST_MAX / 2 ? 2 * next : BRICK_REST_MAX;
+    }
+};
+
 __host__ __device__ constexpr int brick_mail_words(int wsz) { return wsz / 4; }
 
 // ncyc V-cycles from level plan.lm down to the tail and back, on the level's
