@@ -625,7 +625,6 @@ void brick_passes(const Grid &g, bool vel, int wsz, BrickLev &b)
                     }
             }
         }
-        unk_range(g, 0, vel && a == 0, P.xlo, P.xhi);
         P.mail = (unsigned)(a * g.nel * brick_mail_words(wsz));
         P.face_x = vel && a == 0 ? 1 : 0;
     }
@@ -650,17 +649,12 @@ bool plan_bricks(const ibb_ctx *c, bool vel, BrickPlan &P)
     if ((d->smoother_passes != 0 && d->smoother_passes != 2) || d->smoother_zblock > 0) return false;
     P.lc = t.level - 1;
     if (!brick_boxes(c->lv[t.level].g, 16, true, P.lev[t.level])) return false;
-    int lm = -1;
-    for (int l = P.lc; l >= 0; --l) {
-        const Grid &g = c->lv[l].g;
-        if (g.n[0] < 4 || g.n[0] > 1000 || g.n[1] < 4 || (D == 3 && g.n[2] < 4)) break;
-        BrickLev &b = P.lev[l];
-        if (!brick_boxes(g, BRICK_MAX_WG, false, b)) break;
-        // the windows of the levels lie one after the other; a transfer
-        // between q - 1 and q uses the place from the windows of q on: the
-        // residual of the own lines, the x sums around the coarse box (both
-        // for all components at once where that fits, else one by one), or
-        // the coarse iterate around the fine box
+    // The windows of levels l .. lc lie one after the other in the LDS; a
+    // transfer between q - 1 and q uses the place from the windows of q on:
+    // the residual of the own lines, the x sums around the coarse box (both
+    // for all components at once where that fits, else one by one), or the
+    // coarse iterate around the fine box.  The bytes that this takes.
+    auto lay_out = [&](int l) {
         int off = 0, need = 0;
         for (int q = l; q <= t.level; ++q) {
             const Grid &h = c->lv[q].g;
@@ -686,28 +680,22 @@ bool plan_bricks(const ibb_ctx *c, bool vel, BrickPlan &P)
             if (q < t.level) off += ((x.wn * nc * wsz + 15) / 16) * 16;
             need = std::max(need, off);
         }
-        if (need > BRICK_LDS_BUDGET) break;
+        return need;
+    };
+    int lm = -1;
+    for (int l = P.lc; l >= 0; --l) {
+        const Grid &g = c->lv[l].g;
+        if (g.n[0] < 4 || g.n[0] > 1000 || g.n[1] < 4 || (D == 3 && g.n[2] < 4)) break;
+        if (!brick_boxes(g, BRICK_MAX_WG, false, P.lev[l]) || lay_out(l) > BRICK_LDS_BUDGET) break;
         lm = l;
-        P.lds_bytes = need;
     }
     if (lm < 0) return false;
     P.lm = lm;
     for (int l = 0; l < lm; ++l) P.lev[l] = BrickLev{};
-    int off = 0;
+    P.lds_bytes = lay_out(lm);
     P.nwg = 1;
     for (int l = lm; l <= t.level; ++l) {
         BrickLev &x = P.lev[l];
-        x.lds = off;
-        if (l < t.level) {
-            // as laid out above from lm
-            const Grid &f = c->lv[l].g, &h = c->lv[l + 1].g;
-            const BrickLev &y = P.lev[l + 1];
-            const int e1 = h.bc[1] == AX_INOUT ? 1 : 0, e2 = h.bc[2] == AX_INOUT ? 1 : 0;
-            const int own = f.NX * (x.cy + e1) * (D == 3 ? x.cz + e2 : 1) * wsz;
-            const int sums = (h.n[0] + 1) * (2 * (y.cy + e1) + 2) * (D == 3 ? 2 * (y.cz + e2) + 2 : 1) * 8;
-            off += ((x.wn * nc * wsz + 15) / 16) * 16;
-            x.gs = off + nc * std::max(own, sums) <= BRICK_LDS_BUDGET ? nc : 1;
-        }
         {
             const Grid &h = c->lv[l].g;
             const int hx = ((h.bc[0] == AX_INOUT ? h.n[0] : h.n[0] - 1) + 2) >> 1;

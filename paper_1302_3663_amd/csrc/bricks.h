@@ -38,7 +38,6 @@ struct BrickPass {
     int edge;            // the image bits (IMG) that also change the diagonal: axes that do not wrap
     int axis[3];         // the axes: bit position of their image bits
     int walls;           // bit n: the n-th axis has walls at both ends
-    int xlo, xhi;        // unknowns along x
     unsigned mail;       // words from a level's mailboxes to this component's
     int face_x;          // 1: faces along x
 };
