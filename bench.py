@@ -103,8 +103,21 @@ def words_per_unit(site, D, decoupled=False):
     return 3
 
 
-def site_name(site, level, D):
-    return SITES[site][0].replace("D,", f"{D},") + f" (level {level})"
+def site_name(site, level, D, p=None):
+    name = SITES[site][0]
+    if site in (12, 13, 14, 15) and p is not None and level < one_workgroup_start(p, site in (12, 14)):
+        name = name.replace("k_bricks or k_coarse_vcycle", "k_bricks")   # the other begins further down
+    return name.replace("D,", f"{D},") + f" (level {level})"
+
+
+def one_workgroup_start(p, velocity):
+    """first level whose larger colour class of any component fits the 512 threads of the one-workgroup cycle"""
+    level = 0
+    while True:
+        ext = [unknown_extents(p, level, (1 << a) if velocity else 0) for a in range(p["dim"])]
+        if (max(e[0] * e[1] * e[2] for e in ext) + 1) // 2 <= 512:
+            return level
+        level += 1
 
 
 def source_digest():
@@ -129,7 +142,7 @@ def committed_traffic(site, level, workload):
     return float(m_val.group(1))
 
 
-def site_table(prof, D, steps, decoupled=False):
+def site_table(prof, D, steps, p=None, decoupled=False):
     """Rows per launch site and level, largest device time first: launches,
     device ms per step, average launch, algorithmic bytes per launch, the
     bandwidth those bytes imply, and the share of all timed kernels of a step
@@ -140,7 +153,7 @@ def site_table(prof, D, steps, decoupled=False):
         site, level = cls % 32, cls // 32
         bpl = words_per_unit(site, D, decoupled) * SITES[site][1] * v["units"] / v["launches"]
         avg = v["total_ms"] / v["launches"]
-        rows.append(dict(site=site, level=level, kernel=site_name(site, level, D), launches=v["launches"],
+        rows.append(dict(site=site, level=level, kernel=site_name(site, level, D, p), launches=v["launches"],
                          ms_per_step=v["total_ms"] / steps, avg_us=avg * 1e3, bytes_per_launch=bpl,
                          gbs=bpl / (avg * 1e-3) / 1e9 if avg > 0 else 0.0, share=v["total_ms"] / total))
     rows.sort(key=lambda r: -r["ms_per_step"])
@@ -348,7 +361,7 @@ def summarize_counters(pmc_dir, workload, site, level, copy_mib, commands, out_p
     wsize_b = 1024 * mean(k_w, lambda r: r["WRITE_SIZE"]) * w_scale
     D = p["dim"]
     units = {0: None}
-    kernel = site_name(site, level, D)
+    kernel = site_name(site, level, D, p)
     lines = [f"# L2-to-fabric traffic: {kernel}, {workload}", "",
              "Four counter runs of the same command, one counter group each (run from /tmp with TMPDIR=/tmp on "
              "one MI355X, each under `timeout -s KILL 150`):", "", "```"] + commands + ["```", "",
@@ -675,7 +688,7 @@ def main():
             log(f"film, mode {m}: 1 warmup + 1 timed step + 1 kernel-timed step")
             fres[m] = run_mode(fcase, pkg.IBB_FP32_REFINED if m == "refined" else pkg.IBB_FP64, args.inner, 1, 1,
                                log, prof_steps=1)
-            rows, _ = site_table(fres[m]["prof"], 3, 1)
+            rows, _ = site_table(fres[m]["prof"], 3, 1, fcase["params"])
             sites = {}
             for r in rows:
                 if r["level"] == 0 and r["site"] in (0, 2, 4, 23, 24, 25, 26):
@@ -718,7 +731,7 @@ def main():
             high[name]["sites"] = [dict(kernel=t["kernel"], launches=t["launches"], avg_us=round(t["avg_us"], 2),
                                         ms_per_step=round(t["ms_per_step"], 3), share=round(t["share"], 4),
                                         frac=round(t["gbs"] / HBM_PEAK_GBS, 4))
-                                   for t in site_table(r["prof"], 3, 1)[0][:8]]
+                                   for t in site_table(r["prof"], 3, 1, dict(hp, **over))[0][:8]]
         del hcase
     if args.calibrate_copy > 0:
         n = args.calibrate_copy * (1 << 20) // 4
@@ -733,7 +746,7 @@ def main():
     # roofline of the launch site with the largest device time per step in
     # the headline mode (kernel-by-kernel steps after the timed ones)
     D = p["dim"]
-    rows, _ = site_table(head["prof"], D, args.steps)
+    rows, _ = site_table(head["prof"], D, args.steps, p)
     dom = rows[0]
     roof = dict(bound="hbm", achieved=round(dom["gbs"], 1), peak=HBM_PEAK_GBS, unit="GB/s",
                 frac=round(dom["gbs"] / HBM_PEAK_GBS, 4),
@@ -804,7 +817,7 @@ def main():
                       sites=[dict(kernel=t["kernel"], launches=t["launches"], avg_us=round(t["avg_us"], 2),
                                   ms_per_step=round(t["ms_per_step"], 3), share=round(t["share"], 4),
                                   frac=round(t["gbs"] / HBM_PEAK_GBS, 4))
-                             for t in site_table(r["prof"], D, args.steps)[0][:10]])
+                             for t in site_table(r["prof"], D, args.steps, p)[0][:10]])
     if "fp64" in res and "refined" in res:
         out["refined_over_fp64"] = round(res["refined"]["dof_per_s"] / res["fp64"]["dof_per_s"], 3)
     if gcr:

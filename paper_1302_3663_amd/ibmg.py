@@ -72,7 +72,10 @@ def spread_static(params, width, X, F, out=None, stream=None, check=True):
 
 
 class Context:
-    """One biofilm problem resident on a GPU."""
+    """One biofilm problem resident on a GPU, in footprint_bytes of device
+    memory.  Its own solves (not those of its group) take the solver scratch
+    besides (ibb_solver_scratch_bytes), from the first one until close(), if
+    the device has the room; without it they are slower."""
 
     def __init__(self, params, max_nodes, max_springs, precision=L.IBB_FP64, inner_cycles=1, device="cuda:0",
                  stream=None):
@@ -118,6 +121,7 @@ class Context:
         if self.ctx:
             self.lib.ibb_destroy(self.ctx)
             self.ctx = ctypes.c_void_p()
+        self.scratch = None   # its work is done: destroying the context waits for the stream
 
     def __del__(self):
         try:
