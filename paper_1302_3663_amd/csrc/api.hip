@@ -670,6 +670,7 @@ bool plan_bricks(const ibb_ctx *c, bool vel, BrickPlan &P)
                 const int sums = (h.n[0] + 1) * (2 * (x.cy + e1) + 2) * (D == 3 ? 2 * (x.cz + e2) + 2 : 1) * 8;
                 const int one = std::max(own, sums);
                 y.gs = off + nc * one <= BRICK_LDS_BUDGET ? nc : 1;
+                // the most lines a window can take, wherever its box begins
                 const int plines = nc * ((y.cy + 1) / 2 + 4) * (D == 3 ? (y.cz + 1) / 2 + 4 : 1);
                 const int slines = nc * (2 * (x.cy + e1) + 2) * (D == 3 ? 2 * (x.cz + e2) + 2 : 1);
                 const int prl = plines * h.NX * wsz;
@@ -2741,8 +2742,9 @@ ibb_status ibb_spread_static(const ibb_desc *desc, double width, int64_t n, cons
     ph.omega = desc->omega;
     ph.kernel = desc->kernel;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    // the same launches as ibb_spread; the bin counts are cleared by the sort
-    // itself, and every stored face position of the staging is written
+    // the same values as ibb_spread's, every factor worked out where it is
+    // used (there is no room for a table); the bin counts are cleared by the
+    // sort itself, and every stored face position of the staging is written
     // before it is read
     launch_bin_nodes(g, b, X, n > 0 ? n : 1, (int)n, scan_tmp, s);
     long long off = 0;
