@@ -52,9 +52,10 @@ METRIC = "MG solve DOF/s at 1e-10 rel residual, FP32-refined vs FP64; p50/p99 la
 # of its start level) -- the minimum traffic of one pass
 SITES = {
     0: ("k_smooth_u<double>", 8), 1: ("k_smooth_p<double>", 8), 2: ("k_smooth_u<float>", 4),
-    3: ("k_smooth_p<float>", 4), 4: ("k_resid_u<double>", 8), 5: ("k_resid_p<double>", 8),
-    6: ("k_resid_u<float>", 4), 7: ("k_resid_p<float>", 4), 8: ("k_restrict<double>", 8),
-    9: ("k_restrict<float>", 4), 10: ("k_prolong_add<double>", 8), 11: ("k_prolong_add<float>", 4),
+    3: ("k_smooth_p<float>", 4), 4: ("k_resid_u or k_resid_u_rows<double>", 8), 5: ("k_resid_p<double>", 8),
+    6: ("k_resid_u or k_resid_u_rows<float>", 4), 7: ("k_resid_p<float>", 4), 8: ("k_restrict<double>", 8),
+    9: ("k_restrict<float>", 4), 10: ("k_prolong_add or k_prolong_rows<double>", 8),
+    11: ("k_prolong_add or k_prolong_rows<float>", 4),
     # the lower levels of a V-cycle in one launch: as bricks where a context
     # runs them (bricks.hip), in one workgroup (k_coarse_vcycle) elsewhere
     12: ("k_bricks or k_coarse_vcycle<double, D, 1>", 8), 13: ("k_bricks or k_coarse_vcycle<double, D, 0>", 8),
@@ -63,7 +64,7 @@ SITES = {
     18: ("GCR vector passes", 8), 19: ("k_smooth_u_dec<double>", 8), 20: ("k_smooth_u_dec<float>", 4),
     21: ("one-launch sweep (k_smooth_rb, k_smooth_zm)<double>", 8),
     22: ("one-launch sweep (k_smooth_rb, k_smooth_zm)<float>", 4),
-    23: ("k_spread_face", 8), 24: ("k_spread_visc", 8), 25: ("k_interp", 8), 26: ("k_spring_force", 8),
+    23: ("k_spread_face", 8), 24: ("k_spread_visc", 8), 25: ("k_interp or k_interp_w", 8), 26: ("k_spring_force", 8),
     27: ("k_gal_build", 8), 28: ("k_gal_smooth<double>", 8), 29: ("k_gal_smooth<float>", 4),
     30: ("k_gal_resid<double>", 8), 31: ("k_gal_resid<float>", 4),
 }
@@ -107,6 +108,13 @@ def site_name(site, level, D, p=None):
     name = SITES[site][0]
     if site in (12, 13, 14, 15) and p is not None and level < one_workgroup_start(p, site in (12, 14)):
         name = name.replace("k_bricks or k_coarse_vcycle", "k_bricks")   # the other begins further down
+    if site in (4, 6, 10, 11) and p is not None:
+        # by rows from 2^20 points a component on (residual; below, without its norm) or 2^21 (interpolation)
+        ext = [unknown_extents(p, level, 1 << a) for a in range(D)]
+        points = max(e[0] * e[1] * e[2] for e in ext)
+        large = min(e[0] for e in ext) >= 24 and points >= 1 << (20 if site in (4, 6) else 21)
+        if large or site in (10, 11):
+            name = name.split(" or ")[1] if large else name.split(" or ")[0] + name[name.index("<"):]
     return name.replace("D,", f"{D},") + f" (level {level})"
 
 
